@@ -12,12 +12,17 @@ constexpr int kMinLog = 3, kMaxLog = 10, kNumLens = kMaxLog - kMinLog + 1;
 // Sizes with dense Q tables for the matrix (MFMA) paths: 8, 16, 32, 64.
 constexpr int kNumDense = 4;
 
+// Lengths with line-pair tables (line_fft.hpp): 256, 512, 1024.
+constexpr int kNumLineLens = 3;
+
 // Plan-owned device tables (Section 3.2: tables built once, reused by every call).
 struct DeviceTables {
     int device = -1;
     int num_cu = 0;
     float2* tw = nullptr;               // twiddle bank (complex entries)
     int tw_off[kNumLens] = {};          // offset of TwLayout<L> per length
+    float2* line_tab = nullptr;         // tables of the line-pair transforms (line_fft.hpp)
+    int line_off[kNumLineLens] = {};    // offset per length, 256 << i
     // Dense Q_n for the matrix paths, row-major n x n, for n = 8 << i:
     float* q_f32[kNumDense] = {};       // rounded to float32
     uint16_t* q_bf16[kNumDense] = {};   // 3 planes: hi, mid, lo (bf16 bit patterns)
@@ -57,6 +62,11 @@ inline const float2* tw_for(const DeviceTables* t, int L)
     int lg = 0;
     while ((1 << lg) < L) ++lg;
     return t->tw + t->tw_off[lg - kMinLog];
+}
+
+inline const float2* line_tab_for(const DeviceTables* t, int n)
+{
+    return t->line_tab + t->line_off[n == 1024 ? 2 : n == 512 ? 1 : 0];
 }
 
 inline bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }

@@ -20,6 +20,7 @@
 
 #include "dct1d.hpp"
 #include "internal.hpp"
+#include "line_fft.hpp"
 
 namespace dct {
 namespace {
@@ -110,6 +111,28 @@ __global__ void k_twiddles(float2* out, int L)
     }
 }
 
+// Table of the line-pair transforms of length n = r1 r2 16 (layout in line_fft.hpp).
+__global__ void k_line_table(float2* out, int n, int r1)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, T1 = n / r1, T3 = n / 16, TPL = n / 32;
+    double ang, a = 1.0; // the entry is a exp(-i pi ang)
+    if (i < n) {
+        ang = 2.0 * ((i % T1) * (i / T1) % n) / n;
+    } else if (i < n + n / 2) { // slot q of thread t: k = t + T3 q; thread 0, q >= 8: T3 / 2 + T3 (q - 8)
+        const int q = (i - n) / TPL, t = (i - n) % TPL;
+        ang = 0.5 * (T3 * q + (q >= 8 && t == 0 ? T3 / 2 - 8 * T3 : t)) / n;
+        a = 0.5 * sqrt(2.0 / n);
+    } else if (i < n + n / 2 + T1) {
+        const int j = i - n - n / 2;
+        ang = 2.0 * ((j % 16) * (j / 16) % T1) / T1;
+    } else {
+        return;
+    }
+    double s, c;
+    sincospi(ang, &s, &c);
+    out[i] = make_float2((float)(a * c), (float)(-a * s));
+}
+
 __device__ double q_entry(int n, int k, int j)
 {
     const double a = k == 0 ? sqrt(1.0 / n) : sqrt(2.0 / n);
@@ -183,6 +206,13 @@ int tables_init_device(int device)
     }
     const size_t tw_bytes = align_up(tw_entries * sizeof(float2), 256);
     off += tw_bytes;
+    size_t line_entries = 0;
+    for (int i = 0; i < kNumLineLens; ++i) {
+        t->line_off[i] = (int)line_entries;
+        line_entries += (size_t)line_table_size(256 << i);
+    }
+    const size_t line_at = off;
+    off += align_up(line_entries * sizeof(float2), 256);
     size_t dense_off[kNumDense][7];
     for (int i = 0; i < kNumDense; ++i) {
         const size_t nn = (size_t)(8 << i) * (8 << i);
@@ -207,6 +237,11 @@ int tables_init_device(int device)
         const int L = 1 << (i + kMinLog);
         const int size = (L / 8 > 1 ? L / 8 : 1) + L - 1;
         k_twiddles<<<(size + 255) / 256, 256>>>(t->tw + t->tw_off[i], L);
+    }
+    t->line_tab = reinterpret_cast<float2*>(base + line_at);
+    for (int i = 0; i < kNumLineLens; ++i) {
+        const int n = 256 << i, size = line_table_size(n);
+        k_line_table<<<(size + 255) / 256, 256>>>(t->line_tab + t->line_off[i], n, line_plan(n).r1);
     }
     for (int i = 0; i < kNumDense; ++i) {
         const int n = 8 << i;
