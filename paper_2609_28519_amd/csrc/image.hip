@@ -2,14 +2,13 @@
 // multiple of 4): the strided-batch counterpart of the ragged planner's image classes.
 //
 // Shapes whose axes are both powers of two go to the kernels of the basic calls: up to 256
-// the frozen float32-accurate path, with an axis of 512 or 1024 the two-pass long-axis
-// kernels (kern_long.hip, no workspace).  Every other shape (axes that are not powers of
-// two, such as 384 or 600) is computed exactly from the dense Q_n of eq. 1 (FP64-generated,
-// rounded to float32; no zero-padding), one dense product per axis (kern_dense.hip).  A dense pass writes its output tile from whole input rows or
-// columns, so the two (round trip: four) passes ping-pong through a workspace of one
-// float32 image per image of the batch:
-//   forward / inverse   in -> ws (row pass, Q_cols)       ws -> out (column pass, Q_rows)
-//   round trip          in -> ws -> out (forward)          out -> ws -> out (inverse)
+// the frozen float32-accurate path, with an axis of 512 or 1024 the two-pass line kernels
+// (kern_line.hip).  Every other shape is computed exactly, without zero-padding, axis by axis
+// (launch_image): a power-of-two axis by the line kernels, one whose length has small prime
+// factors (384, 600, 1000) by the mixed-radix kernels (kern_mix.hip), each in place on the output;
+// any other length from the dense Q_n of eq. 1 (FP64-generated, rounded to float32,
+// kern_dense.hip).  A dense pass writes its output tile from whole input rows or columns, so it
+// goes through a workspace of one float32 image per image of the batch.
 //
 // dct2d_image_transform takes its workspace from the stream-ordered allocator
 // (hipMallocAsync / hipFreeAsync on the caller's stream, so concurrent calls on different
@@ -75,25 +74,6 @@ int validate(int dir, const float* in, const float* out, int64_t batch, int rows
     return DCT2D_OK;
 }
 
-// The dense passes of `count` images (count <= 65535, the grid's z extent): in and out
-// strided, the workspace packed (rows * cols floats per image).
-int dense_passes(int dir, const float* in, float* out, int64_t count, int rows, int cols, int64_t in_stride,
-                 int64_t out_stride, const float* q_rows, const float* q_cols, float* ws, hipStream_t s)
-{
-    const int64_t n = (int64_t)rows * cols;
-    const Addr in_ws{in, ws, in_stride, n, nullptr, nullptr, nullptr, nullptr};
-    const Addr ws_out{ws, out, n, out_stride, nullptr, nullptr, nullptr, nullptr};
-    const Addr out_ws{out, ws, out_stride, n, nullptr, nullptr, nullptr, nullptr};
-    const bool inv = dir == DCT2D_INVERSE;
-    int rc = launch_dense_axis(in_ws, count, rows, cols, false, inv, q_cols, s);
-    if (rc == DCT2D_OK) rc = launch_dense_axis(ws_out, count, rows, cols, true, inv, q_rows, s);
-    if (dir == DCT2D_ROUNDTRIP) {
-        if (rc == DCT2D_OK) rc = launch_dense_axis(out_ws, count, rows, cols, true, true, q_rows, s);
-        if (rc == DCT2D_OK) rc = launch_dense_axis(ws_out, count, rows, cols, false, true, q_cols, s);
-    }
-    return rc;
-}
-
 // Cached dense Q_n of the current device (allocating entry point only).
 const float* cached_q(int device, int n, int* err)
 {
@@ -137,6 +117,45 @@ float* scratch_ptr(int* err)
 }
 
 } // namespace
+
+int dct::launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows, const float* q_cols)
+{
+    const int64_t n = (int64_t)j.rows * j.cols;
+    const Addr in = j.addr();
+    const Addr out{j.out, j.out, j.out_stride, j.out_stride, j.out_idx, j.out_idx, j.out_slot, j.out_slot};
+    const Addr in_ws{j.in, ws, j.in_stride, n, j.in_idx, nullptr, j.in_slot, nullptr};
+    const Addr ws_out{ws, j.out, n, j.out_stride, nullptr, j.out_idx, nullptr, j.out_slot};
+    const Addr out_ws{j.out, ws, j.out_stride, n, j.out_idx, nullptr, j.out_slot, nullptr};
+    const bool row_line = line_axis(j.cols), col_line = line_axis(j.rows);
+    auto line = [&](const Addr& a, bool column_pass) {
+        return launch_line_axis(t, a, j.batch, j.rows, j.cols, column_pass, j.dir, j.stream);
+    };
+    auto dense = [&](const Addr& a, bool column_pass, bool inverse) {
+        return launch_dense_axis(a, j.batch, j.rows, j.cols, column_pass, inverse, column_pass ? q_rows : q_cols,
+                                 j.stream);
+    };
+    int rc;
+    if (row_line && col_line) {
+        rc = line(in, false);
+        return rc == DCT2D_OK ? line(out, true) : rc;
+    }
+    const bool inv = j.dir == DCT2D_INVERSE;
+    if (j.dir != DCT2D_ROUNDTRIP) {
+        rc = row_line ? line(in_ws, false) : dense(in_ws, false, inv);
+        if (rc != DCT2D_OK) return rc;
+        return col_line ? line(ws_out, true) : dense(ws_out, true, inv);
+    }
+    // round trip: the axes commute (Q_h^T Q_h X Q_w^T Q_w); a line axis is one in-place pass
+    const bool cols_first = !col_line;
+    rc = dense(in_ws, cols_first, false);
+    if (row_line || col_line) {
+        if (rc == DCT2D_OK) rc = dense(ws_out, cols_first, true);
+        return rc == DCT2D_OK ? line(out, col_line) : rc;
+    }
+    if (rc == DCT2D_OK) rc = dense(ws_out, false, false);
+    if (rc == DCT2D_OK) rc = dense(out_ws, false, true);
+    return rc == DCT2D_OK ? dense(ws_out, true, true) : rc;
+}
 
 int dct::image_scratch_init(int device)
 {
@@ -186,18 +205,22 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
         Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
         return launch_long(t, j);
     }
-    const float* q_rows = cached_q(t->device, rows, &rc);
-    const float* q_cols = q_rows ? cached_q(t->device, cols, &rc) : nullptr;
-    if (!q_rows || !q_cols) return rc;
+    Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
+    const bool row_line = line_axis(cols), col_line = line_axis(rows);
+    if (row_line && col_line) return launch_image(t, j, nullptr, nullptr, nullptr);
+    const float *q_rows = nullptr, *q_cols = nullptr;
+    if (!col_line && !(q_rows = cached_q(t->device, rows, &rc))) return rc;
+    if (!row_line && !(q_cols = cached_q(t->device, cols, &rc))) return rc;
     const int64_t n = (int64_t)rows * cols;
-    const int64_t per = batch < 65535 ? batch : 65535;
+    const int64_t per = batch < 65535 ? batch : 65535; // the dense grid's z extent
     float* ws = nullptr;
     if (hipMallocAsync(reinterpret_cast<void**>(&ws), (size_t)(per * n) * sizeof(float), s) != hipSuccess)
         return DCT2D_ERR_NOMEM;
     for (int64_t b0 = 0; b0 < batch && rc == DCT2D_OK; b0 += per) {
-        const int64_t c = batch - b0 < per ? batch - b0 : per;
-        rc = dense_passes(dir, in + b0 * in_stride, out + b0 * out_stride, c, rows, cols, in_stride, out_stride,
-                          q_rows, q_cols, ws, s);
+        j.batch = batch - b0 < per ? batch - b0 : per;
+        j.in = in + b0 * in_stride;
+        j.out = out + b0 * out_stride;
+        rc = launch_image(t, j, ws, q_rows, q_cols);
     }
     if (hipFreeAsync(ws, s) != hipSuccess && rc == DCT2D_OK) rc = DCT2D_ERR_HIP;
     return rc;
@@ -220,27 +243,30 @@ int dct2d_image_transform_noalloc(int dir, const float* in, float* out, int64_t 
         Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
         return launch_long(t, j);
     }
+    Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
+    const bool row_line = line_axis(cols), col_line = line_axis(rows);
+    if (row_line && col_line) return launch_image(t, j, nullptr, nullptr, nullptr);
     float* base = scratch_ptr(&rc);
     if (!base) return rc;
     const size_t n = (size_t)rows * cols;
-    const size_t q_rows_off = 0;
-    const size_t q_cols_off = rows == cols ? 0 : align256((size_t)rows * rows * sizeof(float));
-    const size_t ws_off = align256(q_cols_off + (size_t)cols * cols * sizeof(float));
+    const size_t q_cols_off = col_line || rows == cols ? 0 : align256((size_t)rows * rows * sizeof(float));
+    const size_t ws_off = row_line ? q_cols_off : align256(q_cols_off + (size_t)cols * cols * sizeof(float));
     if (ws_off + n * sizeof(float) > kScratchBytes) return DCT2D_ERR_SIZE; // not reached for accepted shapes
     const int64_t fit = (int64_t)((kScratchBytes - ws_off) / (n * sizeof(float)));
     const int64_t per = fit < 65535 ? fit : 65535;
     char* b = reinterpret_cast<char*>(base);
-    float* q_rows = reinterpret_cast<float*>(b + q_rows_off);
+    float* q_rows = reinterpret_cast<float*>(b);
     float* q_cols = reinterpret_cast<float*>(b + q_cols_off);
     float* ws = reinterpret_cast<float*>(b + ws_off);
     // the tables are rebuilt on the caller's stream every call: the scratch keeps whatever
     // the previous call on this device left in it
-    rc = tables_dense_q(rows, q_rows, s);
-    if (rc == DCT2D_OK && cols != rows) rc = tables_dense_q(cols, q_cols, s);
+    if (!col_line) rc = tables_dense_q(rows, q_rows, s);
+    if (rc == DCT2D_OK && !row_line && cols != rows) rc = tables_dense_q(cols, q_cols, s);
     for (int64_t b0 = 0; b0 < batch && rc == DCT2D_OK; b0 += per) {
-        const int64_t c = batch - b0 < per ? batch - b0 : per;
-        rc = dense_passes(dir, in + b0 * in_stride, out + b0 * out_stride, c, rows, cols, in_stride, out_stride,
-                          q_rows, q_cols, ws, s);
+        j.batch = batch - b0 < per ? batch - b0 : per;
+        j.in = in + b0 * in_stride;
+        j.out = out + b0 * out_stride;
+        rc = launch_image(t, j, ws, q_rows, q_cols);
     }
     return rc;
 }

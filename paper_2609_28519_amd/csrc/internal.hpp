@@ -23,6 +23,7 @@ struct DeviceTables {
     int tw_off[kNumLens] = {};          // offset of TwLayout<L> per length
     float2* line_tab = nullptr;         // tables of the line-pair transforms (line_fft.hpp)
     int line_off[kNumLineLens] = {};    // offset per length, 256 << i
+    float2* mix_tab = nullptr;          // tables of the mixed-radix transforms, every length (mix_fft.hpp)
     // Dense Q_n for the matrix paths, row-major n x n, for n = 8 << i:
     float* q_f32[kNumDense] = {};       // rounded to float32
     uint16_t* q_bf16[kNumDense] = {};   // 3 planes: hi, mid, lo (bf16 bit patterns)
@@ -181,6 +182,19 @@ int launch_short_line_pass(const DeviceTables* t, const Addr& a, int64_t batch, 
 // Power-of-two shapes with an axis of 512 or 1024, the other 8 .. 1024 (kern_long.hip): a row
 // pass and a column pass, the second in place on the output.
 int launch_long(const DeviceTables* t, const Job& j);
+// A pass of direction `dir` along the rows or the columns of rows x cols arrays (cols a multiple of
+// 4), whose length has small prime factors only (mix_smooth), in place or not (kern_mix.hip).
+bool mix_smooth(int n);
+int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass, int dir,
+                    hipStream_t s);
+// The same along an axis of any length that transforms its lines in place: powers of two and
+// lengths with small prime factors (line_axis).
+bool line_axis(int n);
+int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass,
+                     int dir, hipStream_t s);
+// Whole images (both axes in [8, 1024], not both powers of two).  Axes outside line_axis take a dense
+// product: they need the length's Q and a workspace of rows * cols floats per image.
+int launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows, const float* q_cols);
 // Rectangles with one axis of 256 and the other at most 128, fused (kern_rect256.hip).
 int launch_rect256(const DeviceTables* t, const Job& j);
 int fp32_variant_count(int rows, int cols, int dir);

@@ -272,10 +272,17 @@ int run_cols(const DeviceTables* t, const Addr& a, int64_t batch, int cols, int 
                                 : run<N, DCT2D_INVERSE, true, 8>(t, a, batch, cols, cols, 1, s);
 }
 
-int axis_pass(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass, int dir,
-              hipStream_t s)
+} // namespace
+
+bool line_axis(int n) { return is_pow2(n) || mix_smooth(n); }
+
+int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass,
+                     int dir, hipStream_t s)
 {
     const int len = column_pass ? rows : cols;
+    // a pair of rows needs an even number of them; k_mix takes any
+    if (!is_pow2(len) || (len >= 256 && !column_pass && (rows & 1)))
+        return launch_mix_axis(t, a, batch, rows, cols, column_pass, dir, s);
     switch (len) {
     case 1024:
         return column_pass ? run_cols<1024>(t, a, batch, cols, dir, s)
@@ -283,14 +290,12 @@ int axis_pass(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int
     case 512:
         return column_pass ? run_cols<512>(t, a, batch, cols, dir, s)
                            : run_dir<512, false, 1>(t, a, batch, rows, 1, cols, dir, s);
-    case 256: // the other axis is 512 or 1024
+    case 256:
         return column_pass ? run_cols<256>(t, a, batch, cols, dir, s)
                            : run_dir<256, false, 1>(t, a, batch, rows, 1, cols, dir, s);
     default: return launch_short_line_pass(t, a, batch, len, column_pass ? cols : rows, column_pass, dir, s);
     }
 }
-
-} // namespace
 
 int launch_long(const DeviceTables* t, const Job& j)
 {
@@ -298,8 +303,8 @@ int launch_long(const DeviceTables* t, const Job& j)
     const Addr first = j.addr();
     const Addr in_place{j.out, j.out, j.out_stride, j.out_stride, j.out_idx, j.out_idx, j.out_slot, j.out_slot};
     // rows first (input -> output), then columns in place on the output
-    int rc = axis_pass(t, first, j.batch, j.rows, j.cols, false, j.dir, j.stream);
-    if (rc == DCT2D_OK) rc = axis_pass(t, in_place, j.batch, j.rows, j.cols, true, j.dir, j.stream);
+    int rc = launch_line_axis(t, first, j.batch, j.rows, j.cols, false, j.dir, j.stream);
+    if (rc == DCT2D_OK) rc = launch_line_axis(t, in_place, j.batch, j.rows, j.cols, true, j.dir, j.stream);
     return rc;
 }
 

@@ -6,9 +6,9 @@
 // configuration of the frozen per-size policy (the same table the autotuner fills for
 // the basic calls, Section 3.2: variants fixed before measurement), with grid-stride
 // schedules replaced by one tile per workgroup, since the classes share the GPU.  Image classes
-// with power-of-two axes and an axis of 512 or 1024 run the two-pass long-axis kernels in
-// place on the batch (no workspace); image classes with an axis that is not a power of two
-// (such as 384) get dense float32 Q tables and a workspace.  The whole batch is then
+// run pass by pass in place on the batch, power-of-two axes and axes with small prime factors
+// (such as 384) without a workspace; axes of any other length get dense float32 Q tables and the
+// class a workspace.  The whole batch is then
 // recorded once into a HIP graph: one fork-join branch per class, so independent
 // classes run concurrently.  Kernels read the batch base pointer from a plan-owned
 // device slot, so the recorded graph replays on any buffer.
@@ -33,7 +33,7 @@ struct ClassRec {
     int rows, cols;
     int64_t count;
     int64_t* d_off = nullptr; // device offsets (floats from base)
-    bool dense = false;       // dense axis passes through the workspace
+    bool image = false;       // an axis that is not a power of two (launch_image)
     bool long_axes = false;   // two-pass long-axis kernels (an axis of 512 or 1024)
     float* q_rows = nullptr;  // dense Q_rows (column pass)
     float* q_cols = nullptr;  // dense Q_cols (row pass)
@@ -50,7 +50,9 @@ bool long_shape(int r, int c)
     return is_pow2(r) && is_pow2(c) && r >= 8 && c >= 8 && r <= 1024 && c <= 1024 && (r > 256 || c > 256);
 }
 
-bool dense_shape(int r, int c) { return !fast_shape(r, c) && !long_shape(r, c); }
+bool image_shape(int r, int c) { return !fast_shape(r, c) && !long_shape(r, c); }
+// an axis that takes a dense product, which cannot run in place
+bool workspace_shape(int r, int c) { return image_shape(r, c) && !(line_axis(r) && line_axis(c)); }
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -95,7 +97,7 @@ void release(dct2d_ragged_plan* p)
 // Records the work of one class on stream s.
 int record_class(const DeviceTables* t, dct2d_ragged_plan* p, const ClassRec& c, hipStream_t s)
 {
-    if (!c.dense) {
+    if (!c.image) {
         Job j{p->dir, nullptr, nullptr, c.count, c.rows, c.cols, 0, 0, s, 0};
         j.in_idx = j.out_idx = c.d_off;
         j.in_slot = j.out_slot = p->d_slot;
@@ -104,30 +106,10 @@ int record_class(const DeviceTables* t, dct2d_ragged_plan* p, const ClassRec& c,
         if (c.long_axes) return launch_long(t, j);
         return dispatch(t, j, p->prec);
     }
-    // dense image passes: base(indexed) <-> workspace(packed), ping-pong
-    const int64_t n = (int64_t)c.rows * c.cols;
-    const Addr to_ws{nullptr, c.ws, 0, n, c.d_off, nullptr, p->d_slot, nullptr};
-    const Addr to_base{c.ws, nullptr, n, 0, nullptr, c.d_off, nullptr, p->d_slot};
-    const Addr base_to_ws = to_ws, ws_to_base = to_base;
-    int rc;
-    switch (p->dir) {
-    case DCT2D_FORWARD:
-        rc = launch_dense_axis(base_to_ws, c.count, c.rows, c.cols, false, false, c.q_cols, s);
-        if (rc) return rc;
-        return launch_dense_axis(ws_to_base, c.count, c.rows, c.cols, true, false, c.q_rows, s);
-    case DCT2D_INVERSE:
-        rc = launch_dense_axis(base_to_ws, c.count, c.rows, c.cols, false, true, c.q_cols, s);
-        if (rc) return rc;
-        return launch_dense_axis(ws_to_base, c.count, c.rows, c.cols, true, true, c.q_rows, s);
-    default:
-        rc = launch_dense_axis(base_to_ws, c.count, c.rows, c.cols, false, false, c.q_cols, s);
-        if (rc) return rc;
-        rc = launch_dense_axis(ws_to_base, c.count, c.rows, c.cols, true, false, c.q_rows, s);
-        if (rc) return rc;
-        rc = launch_dense_axis(base_to_ws, c.count, c.rows, c.cols, true, true, c.q_rows, s);
-        if (rc) return rc;
-        return launch_dense_axis(ws_to_base, c.count, c.rows, c.cols, false, true, c.q_cols, s);
-    }
+    Job j{p->dir, nullptr, nullptr, c.count, c.rows, c.cols, 0, 0, s, 0};
+    j.in_idx = j.out_idx = c.d_off;
+    j.in_slot = j.out_slot = p->d_slot;
+    return launch_image(t, j, c.ws, c.q_rows, c.q_cols);
 }
 
 } // namespace
@@ -179,16 +161,16 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     std::map<int, size_t> qoff;
     for (auto& g : groups) bytes = align256(bytes + g.second.size() * sizeof(int64_t));
     for (auto& g : groups) {
-        if (!dense_shape(g.first.first, g.first.second)) continue;
+        if (!image_shape(g.first.first, g.first.second)) continue;
         for (int L : {g.first.first, g.first.second})
-            if (!qoff.count(L)) {
+            if (!line_axis(L) && !qoff.count(L)) {
                 qoff[L] = bytes;
                 bytes = align256(bytes + (size_t)L * L * 4);
             }
     }
     std::vector<size_t> wsoff;
     for (auto& g : groups) {
-        if (!dense_shape(g.first.first, g.first.second)) {
+        if (!workspace_shape(g.first.first, g.first.second)) {
             wsoff.push_back(0);
             continue;
         }
@@ -217,11 +199,11 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
             return DCT2D_ERR_HIP;
         }
         c.long_axes = long_shape(c.rows, c.cols);
-        if (dense_shape(c.rows, c.cols)) {
-            c.dense = true;
-            c.q_rows = reinterpret_cast<float*>(base + qoff[c.rows]);
-            c.q_cols = reinterpret_cast<float*>(base + qoff[c.cols]);
-            c.ws = reinterpret_cast<float*>(base + wsoff[gi]);
+        if (image_shape(c.rows, c.cols)) {
+            c.image = true;
+            if (!line_axis(c.rows)) c.q_rows = reinterpret_cast<float*>(base + qoff[c.rows]);
+            if (!line_axis(c.cols)) c.q_cols = reinterpret_cast<float*>(base + qoff[c.cols]);
+            if (workspace_shape(c.rows, c.cols)) c.ws = reinterpret_cast<float*>(base + wsoff[gi]);
         }
         p->cls.push_back(c);
         ++gi;

@@ -21,6 +21,7 @@
 #include "dct1d.hpp"
 #include "internal.hpp"
 #include "line_fft.hpp"
+#include "mix_fft.hpp"
 
 namespace dct {
 namespace {
@@ -133,6 +134,20 @@ __global__ void k_line_table(float2* out, int n, int r1)
     out[i] = make_float2((float)(a * c), (float)(-a * s));
 }
 
+// Tables of the mixed-radix transforms: length 8 + blockIdx.x (layout in mix_fft.hpp).
+__global__ void k_mix_tables(float2* out)
+{
+    const int n = 8 + blockIdx.x;
+    out += mix_table_offset(n);
+    for (int i = threadIdx.x; i < mix_table_size(n); i += blockDim.x) {
+        const int k = i - n;
+        const double a = k < 0 ? 1.0 : 0.5 * (k == 0 ? sqrt(1.0 / n) : sqrt(2.0 / n));
+        double s, c;
+        sincospi(k < 0 ? 2.0 * i / n : 0.5 * k / n, &s, &c);
+        out[i] = make_float2((float)(a * c), (float)(-a * s));
+    }
+}
+
 __device__ double q_entry(int n, int k, int j)
 {
     const double a = k == 0 ? sqrt(1.0 / n) : sqrt(2.0 / n);
@@ -213,6 +228,8 @@ int tables_init_device(int device)
     }
     const size_t line_at = off;
     off += align_up(line_entries * sizeof(float2), 256);
+    const size_t mix_at = off;
+    off += align_up((size_t)mix_table_offset(1025) * sizeof(float2), 256);
     size_t dense_off[kNumDense][7];
     for (int i = 0; i < kNumDense; ++i) {
         const size_t nn = (size_t)(8 << i) * (8 << i);
@@ -243,6 +260,8 @@ int tables_init_device(int device)
         const int n = 256 << i, size = line_table_size(n);
         k_line_table<<<(size + 255) / 256, 256>>>(t->line_tab + t->line_off[i], n, line_plan(n).r1);
     }
+    t->mix_tab = reinterpret_cast<float2*>(base + mix_at);
+    k_mix_tables<<<1017, 256>>>(t->mix_tab);
     for (int i = 0; i < kNumDense; ++i) {
         const int n = 8 << i;
         t->q_f32[i] = reinterpret_cast<float*>(base + dense_off[i][0]);
