@@ -12,8 +12,8 @@ constexpr int kMinLog = 3, kMaxLog = 10, kNumLens = kMaxLog - kMinLog + 1;
 // Sizes with dense Q tables for the matrix (MFMA) paths: 8, 16, 32, 64.
 constexpr int kNumDense = 4;
 
-// Lengths with line-pair tables (line_fft.hpp): 256, 512, 1024.
-constexpr int kNumLineLens = 3;
+// Lengths with line-pair tables (line_fft.hpp): 32 .. 1024.
+constexpr int kNumLineLens = 6;
 
 // Plan-owned device tables (Section 3.2: tables built once, reused by every call).
 struct DeviceTables {
@@ -22,7 +22,7 @@ struct DeviceTables {
     float2* tw = nullptr;               // twiddle bank (complex entries)
     int tw_off[kNumLens] = {};          // offset of TwLayout<L> per length
     float2* line_tab = nullptr;         // tables of the line-pair transforms (line_fft.hpp)
-    int line_off[kNumLineLens] = {};    // offset per length, 256 << i
+    int line_off[kNumLineLens] = {};    // offset per length, 32 << i
     float2* mix_tab = nullptr;          // tables of the mixed-radix transforms, every length (mix_fft.hpp)
     // Dense Q_n for the matrix paths, row-major n x n, for n = 8 << i:
     float* q_f32[kNumDense] = {};       // rounded to float32
@@ -67,7 +67,9 @@ inline const float2* tw_for(const DeviceTables* t, int L)
 
 inline const float2* line_tab_for(const DeviceTables* t, int n)
 {
-    return t->line_tab + t->line_off[n == 1024 ? 2 : n == 512 ? 1 : 0];
+    int i = 0;
+    while ((32 << i) < n) ++i;
+    return t->line_tab + t->line_off[i];
 }
 
 inline bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
@@ -197,6 +199,9 @@ int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int ro
 int launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows, const float* q_cols);
 // Rectangles with one axis of 256 and the other at most 128, fused (kern_rect256.hip).
 int launch_rect256(const DeviceTables* t, const Job& j);
+// One array per workgroup in registers, both axes 32 .. 256 and one of 128 or 256 (kern_tile.hip).
+bool tile_shape(int rows, int cols);
+int launch_tile(const DeviceTables* t, const Job& j, bool persistent);
 int fp32_variant_count(int rows, int cols, int dir);
 int fp32_default_variant(int rows, int cols, int dir);
 int fp32_unshared_variant(int rows, int cols, int variant);

@@ -1700,14 +1700,21 @@ int launch_fused(const DeviceTables* t, const Job& j)
 //                     1 two-pass; 2 as 0 with resident workgroups looping over the tiles;
 //                     3 (short axis <= 64) k_rect256_db: one persistent workgroup per CU, two
 //                     tile buffers filled by LDS DMA while the other is transformed
+//   after these, where tile_shape holds: k_tile (kern_tile.hip), one array per workgroup, and then the
+//                     same with resident workgroups looping over the arrays
+int fp32_tile_variant(int rows, int cols)
+{
+    if (rows == 128 && cols == 128) return 6;
+    if (rows <= 128 && cols <= 128) return 2;
+    if (rows == 256 && cols == 256) return 5;
+    return (rows == 256 ? cols : rows) <= 64 ? 4 : 3; // variant 3 of k_rect256: short axis <= 64 only
+}
+
 int fp32_variant_count(int rows, int cols, int)
 {
     if (rows == 64 && cols == 64) return 16;
     if (rows <= 64 && cols <= 64) return 13;
-    if (rows == 128 && cols == 128) return 6;
-    if (rows <= 128 && cols <= 128) return 2;
-    if (rows == 256 && cols == 256) return 5;
-    return (rows == 256 ? cols : rows) <= 64 ? 4 : 3; // variant 3: short axis <= 64 only
+    return fp32_tile_variant(rows, cols) + (tile_shape(rows, cols) ? 2 : 0);
 }
 
 // Variant used until the tuner measures otherwise (fastest in measurements on MI355X
@@ -1715,8 +1722,8 @@ int fp32_variant_count(int rows, int cols, int)
 // with at most 16 workgroups per CU; 32 at most 10 per CU, staged for the round trip;
 // 64 x 64 the two-wavefront split kernel, with at most 4 workgroups per CU for forward and
 // inverse.  Rectangles with a longer axis of 32: staged, at most 16 per CU; of 64: staged,
-// uncapped (a short axis leaves most lanes of one pass idle, so more resident tiles pay).  The staged split kernel for 128 x 128 with one array per workgroup, the split
-// kernel for 256 x 256 with its two cohorts of CUs staggered by about 6 x 8k cycles.
+// uncapped (a short axis leaves most lanes of one pass idle, so more resident tiles pay).  The staged split kernel for 128 x 128 with one array per workgroup; the
+// whole-array register kernel for the other shapes with an axis of 128 or 256 and none below 32.
 int fp32_default_variant(int rows, int cols, int dir)
 {
     if (rows <= 64 && cols <= 64) {
@@ -1727,14 +1734,19 @@ int fp32_default_variant(int rows, int cols, int dir)
         return m <= 8 ? 4 : m <= 16 ? 6 : m <= 32 ? (rt ? 8 : 7) : (rt ? 4 : 12);
     }
     if (rows == 128 && cols == 128) return 4;
-    if (rows == 256 && cols == 256) return 4;
+    if (tile_shape(rows, cols)) {
+        const int tile = fp32_tile_variant(rows, cols);
+        // 256 x 256 forward: resident workgroups, whose next array's loads overlap the stores (265 us
+        // against 277 per 2^27 floats; inverse and round trip equal, every other shape slower)
+        if (rows == 256 && cols == 256) return dir == DCT2D_FORWARD ? tile + 1 : tile;
+        // the inverse of tall arrays runs as fast in k_rect256_db (256 x 64 260 against 262 us, 256 x 32 251
+        // against 252)
+        return rows == 256 && cols <= 64 && dir == DCT2D_INVERSE ? 3 : tile;
+    }
     if ((rows == 256) != (cols == 256)) {
-        // measured on 512 MiB batches: the double-buffered kernel wherever it leads
-        const bool wide = cols == 256;
-        const int s = wide ? rows : cols;
-        if (s == 128) return dir == DCT2D_FORWARD ? 1 : wide ? 0 : 2;
-        if (dir != DCT2D_ROUNDTRIP) return 3;
-        return wide || s >= 32 ? 0 : 3; // the round trip's arithmetic wants two workgroups per CU
+        // the other axis is 8 or 16; measured on 512 MiB batches: the double-buffered kernel wherever it
+        // leads, but the round trip's arithmetic wants two workgroups per CU
+        return dir == DCT2D_ROUNDTRIP && cols == 256 ? 0 : 3;
     }
     return 0;
 }
@@ -1748,6 +1760,7 @@ int fp32_default_variant(int rows, int cols, int dir)
 int fp32_unshared_variant(int rows, int cols, int v)
 {
     if (rows <= 64 && cols <= 64) return v == 0 ? 3 : v;
+    if (tile_shape(rows, cols) && v > fp32_tile_variant(rows, cols)) return v - 1;
     if (rows == 128 && cols == 128) return v == 0 ? 5 : v == 3 ? 4 : v;
     if (rows == 256 && cols == 256) return v == 0 || v == 3 || v == 4 ? 2 : v;
     if ((rows == 256) != (cols == 256)) return v == 2 || v == 3 ? 0 : v;
@@ -1762,6 +1775,8 @@ int launch_fp32(const DeviceTables* t, const Job& j)
         if (j.variant == 1) return launch_fused(t, j);
         return launch_two_pass(t, j);
     }
+    const int tile = fp32_tile_variant(j.rows, j.cols);
+    if (j.variant >= tile) return launch_tile(t, j, j.variant > tile);
     if (j.rows == 128 && j.cols == 128) {
         if (j.variant == 0 || j.variant >= 3) return launch_split128(t, j, j.variant == 3 || j.variant == 4);
         if (j.variant == 1) return launch_fused(t, j);

@@ -113,23 +113,14 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
             *reinterpret_cast<gfloat*>(dst + c * 4 + (o + (uint32_t)ls * 4u)) = xb;
         }
     };
-    // Coefficient slots (line_fft.hpp): k_lo = lane part + constant, k_hi = N - k_lo likewise, the
-    // lane parts never negative (they go into unsigned 32-bit offsets).
-    auto lo_lane = [&](int q) { return q < 8 ? t : (t0 ? C::T3 / 2 : t + 8 * C::T3); };
-    auto lo_const = [&](int q) { return C::T3 * (q & 7); };
-    auto hi_lane = [&](int q) {
-        return q == 0 ? (t0 ? 0 : N / 2 - t) : q < 8 ? C::TPL - t : (t0 ? 8 * C::T3 + C::TPL - C::T3 / 2 : C::TPL - t);
-    };
-    auto hi_const = [&](int q) { return q == 0 ? N / 2 : N - C::TPL - C::T3 * q; };
-    // x[2n] of stage-1 butterfly i: n = r1 + T1 m, r1 = t + TPL i, or its mirror T1 - 1 - that
-    auto n_lane = [&](int i) { return i < NB / 2 ? 2 * t : 2 * (C::TPL - 1 - t); };
-    auto n_const = [&](int i) { return 2 * C::TPL * (i < NB / 2 ? i : NB - 1 - (i - NB / 2)); };
+    auto lo_lane = [&](int q) { return line::lo_lane<N>(t, q); };
+    auto hi_lane = [&](int q) { return line::hi_lane<N>(t, q); };
     if constexpr (DIR == DCT2D_INVERSE) {
         cf lo[16], hi[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            lo[q] = load_k(lane(lo_lane(q)), lo_const(q));
-            hi[q] = load_k(lane(hi_lane(q)), hi_const(q));
+            lo[q] = load_k(lane(lo_lane(q)), line::lo_const<N>(q));
+            hi[q] = load_k(lane(hi_lane(q)), line::hi_const<N>(q));
         }
 #pragma unroll
         for (int i = 0; i < COPIES; ++i) *(reinterpret_cast<float4*>(lds_all) + tc_at(i)) = tc[i];
@@ -147,12 +138,11 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
         // x[2n], x[2n+1] for n = r1 + T1 m, m < R1 / 2, r1 over the thread's butterflies
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            constexpr int H = NB / 2;
-            const int mi = i < H ? i + H : i - H; // the mirrored butterfly
-            const uint32_t o_in = lane(n_lane(i));
+            const int mi = line::mirror<N>(i);
+            const uint32_t o_in = lane(line::n_lane<N>(t, i));
 #pragma unroll
             for (int m = 0; m < R1 / 2; ++m) {
-                const int c = n_const(i) + 2 * C::T1 * m;
+                const int c = line::n_const<N>(i, m);
                 cf e, o;
                 if constexpr (COLS) {
                     e = load_k(o_in, c);
@@ -180,8 +170,8 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
             if constexpr (DIR == DCT2D_ROUNDTRIP) {
                 line::slot_inverse<N>(xa, xb, q == 0 && t0, c, s0, lo[q], hi[q]);
             } else if constexpr (COLS) {
-                store_k(lane(lo_lane(q)), lo_const(q), xa.x, xb.x);
-                store_k(lane(hi_lane(q)), hi_const(q), xa.y, xb.y);
+                store_k(lane(lo_lane(q)), line::lo_const<N>(q), xa.x, xb.x);
+                store_k(lane(hi_lane(q)), line::hi_const<N>(q), xa.y, xb.y);
             } else {
                 lo[q] = xa;
                 hi[q] = xb;
@@ -195,8 +185,8 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
                     const cf x = l ? hi[q] : lo[q];
-                    row[lo_lane(q) + lo_const(q)] = x.x;
-                    row[hi_lane(q) + hi_const(q)] = x.y;
+                    row[lo_lane(q) + line::lo_const<N>(q)] = x.x;
+                    row[hi_lane(q) + line::hi_const<N>(q)] = x.y;
                 }
                 sync();
                 const uint32_t o = lane(4 * t) + (l ? (uint32_t)ls * 4u : 0u);
@@ -214,12 +204,11 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
     line::fft_inverse<N, P>(v, lds, t, ps, tw, sync);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        constexpr int H = NB / 2;
-        const int mi = i < H ? i + H : i - H;
-        const uint32_t o_out = lane(n_lane(i));
+        const int mi = line::mirror<N>(i);
+        const uint32_t o_out = lane(line::n_lane<N>(t, i));
 #pragma unroll
         for (int m = 0; m < R1 / 2; ++m) {
-            const int c = n_const(i) + 2 * C::T1 * m;
+            const int c = line::n_const<N>(i, m);
             const cf e = v[i * R1 + m], o = v[mi * R1 + R1 - 1 - m];
             if constexpr (COLS) {
                 store_k(o_out, c, e.x, e.y);

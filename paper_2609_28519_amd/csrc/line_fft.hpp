@@ -142,16 +142,17 @@ typedef const DCT_GLOBAL float2* tabptr;
 //   exchange 1, (p, r1) at p * PITCH1 + r1: written and read along r1 (the read side of N = 1024
 //     spans two p per 32 lanes, 8 banks apart: two lanes share 8 of the banks)
 //   exchange 2, (j3, r2) at 17 j3 + r2: written along r2, read along j3
-// Rows: the pair slots one after another, SLOT apart (32 / TPL slots per 32 lanes, TPL banks
-// apart); columns: the slots fastest.
+// Rows: the pair slots one after another, SLOT apart, an odd multiple of TPL modulo 32 (the 32 / TPL
+// slots of 32 lanes then cover all banks); columns: the slots fastest.
+constexpr int spread(int size, int tpl) { return size % (2 * tpl) == tpl ? size : spread(size + 1, tpl); }
 template <int N, bool COLS, int SLOTS>
 struct Place {
     using C = LineCfg<N>;
     static constexpr int PITCH1 = !COLS && N == 1024 ? C::T1 + 8 : C::T1;
     static constexpr int EX1 = C::R2 > 1 ? C::R1 * PITCH1 : 0, EX2 = C::T3 * 17;
     static constexpr int SIZE = EX1 > EX2 ? EX1 : EX2;
-    static constexpr int SLOT = COLS ? SIZE : C::TPL >= 32 ? SIZE : (SIZE + 31) / 32 * 32 + C::TPL;
-    static constexpr int FLOATS = SLOT * SLOTS;
+    static constexpr int SLOT = COLS || C::TPL >= 32 ? SIZE : spread(SIZE, C::TPL);
+    static constexpr int FLOATS = C::TPL > 1 ? SLOT * SLOTS : 0; // one thread has the whole pair
     __device__ static int at(int e, int ps) { return COLS ? e * SLOTS + ps : ps * SLOT + e; }
     __device__ static int ex1(int p, int r1, int ps) { return at(p * PITCH1 + r1, ps); }
     __device__ static int ex2(int j3, int r2, int ps) { return at(17 * j3 + r2, ps); }
@@ -253,6 +254,12 @@ __device__ __forceinline__ void fft_forward(cf (&v)[32], float* lds, int t, int 
         exchange(
             lds, v, [&](int i) { return P::ex2(Mid<N>::p(t, i) + R1 * (i % R2), Mid<N>::r2(t), ps); },
             [&](int i) { return P::ex2(j3_of<N>(t, i / 16), i % 16, ps); }, sync);
+    } else if constexpr (C::TPL == 1) {
+        cf u[32]; // one thread has the whole pair: r1 = i, or 15 - (i - 8)
+#pragma unroll
+        for (int i = 0; i < 32; ++i) u[16 * (i % R1) + (i / R1 < 8 ? i / R1 : 23 - i / R1)] = v[i];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = u[i];
     } else {
         exchange(
             lds, v, [&](int i) { return P::ex2(i % R1, r1_of<N>(t, i / R1), ps); },
@@ -283,6 +290,12 @@ __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int 
         exchange(
             lds, v, [&](int i) { return P::ex1(Mid<N>::p(t, i), Mid<N>::r2(t) + 16 * (i % R2), ps); },
             [&](int i) { return P::ex1(i % R1, r1_of<N>(t, i / R1), ps); }, sync);
+    } else if constexpr (C::TPL == 1) {
+        cf u[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) u[i] = v[16 * (i % R1) + (i / R1 < 8 ? i / R1 : 23 - i / R1)];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = u[i];
     } else {
         exchange(
             lds, v, [&](int i) { return P::ex2(j3_of<N>(t, i / 16), i % 16, ps); },
@@ -295,20 +308,42 @@ __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int 
     }
 }
 
-// Slot q of the thread's 16 coefficient pairs (k, N-k).  Threads t > 0: k = t + T3 q, the partner
-// in the mirrored butterfly.  Thread 0 holds butterflies 0 and T3/2, each its own mirror: slots 0-7
-// are k = T3 q (slot 0: the two unpaired coefficients 0 and N/2), slots 8-15 k = T3/2 + T3 (q - 8).
+// Slot q of the thread's 16 coefficient pairs (k_lo, k_hi = N - k_lo): k_lo = t + T3 q, the partner in
+// the mirrored butterfly.  Thread 0 holds butterflies 0 and T3/2, each its own mirror: slots 0-7 are
+// k_lo = T3 q (slot 0: the two unpaired coefficients 0 and N/2), slots 8-15 k_lo = T3/2 + T3 q.  So
+// k_lo < N/2 exactly for q < 8.
+
+// The same indices as a non-negative lane part plus a constant (32-bit unsigned offsets).
+// Sample x[2n] (with x[2n+1]) of stage-1 butterfly i, member m < R1 / 2: 2n = n_lane + n_const.
 template <int N>
-__device__ __forceinline__ int k_lo(int t, int q)
+__device__ __forceinline__ int n_lane(int t, int i)
+{
+    return i < LineCfg<N>::NB / 2 ? 2 * t : 2 * (LineCfg<N>::TPL - 1 - t);
+}
+template <int N>
+__host__ __device__ constexpr int n_const(int i, int m)
 {
     using C = LineCfg<N>;
-    return C::T3 * q + (q < 8 || t != 0 ? t : C::T3 / 2 - 8 * C::T3);
+    return 2 * C::TPL * (i < C::NB / 2 ? i : C::NB - 1 - (i - C::NB / 2)) + 2 * C::T1 * m;
+}
+// The butterfly that owns x[2n+1] (as its member R1 - 1 - m).
+template <int N>
+__host__ __device__ constexpr int mirror(int i)
+{
+    return i < LineCfg<N>::NB / 2 ? i + LineCfg<N>::NB / 2 : i - LineCfg<N>::NB / 2;
+}
+// Coefficients of slot q: k_lo = lo_lane + lo_const, k_hi = hi_lane + hi_const.
+template <int N>
+__device__ __forceinline__ int lo_lane(int t, int q) { return q < 8 || t != 0 ? t : LineCfg<N>::T3 / 2; }
+template <int N>
+__host__ __device__ constexpr int lo_const(int q) { return LineCfg<N>::T3 * q; }
+template <int N>
+__device__ __forceinline__ int hi_lane(int t, int q)
+{
+    return q == 0 ? (t == 0 ? 0 : N / 2 - t) : LineCfg<N>::TPL - lo_lane<N>(t, q);
 }
 template <int N>
-__device__ __forceinline__ int k_hi(int t, int q)
-{
-    return q == 0 && t == 0 ? N / 2 : N - k_lo<N>(t, q);
-}
+__host__ __device__ constexpr int hi_const(int q) { return q == 0 ? N / 2 : N - LineCfg<N>::TPL - LineCfg<N>::T3 * q; }
 
 __device__ __forceinline__ cf pick(bool c, cf a, cf b) { return {c ? a.x : b.x, c ? a.y : b.y}; }
 
@@ -319,8 +354,8 @@ __device__ __forceinline__ void to_slots(const cf (&v)[32], bool t0, cf (&lo)[16
     for (int q = 0; q < 8; ++q) {
         lo[q] = v[q];
         hi[q] = pick(t0, q == 0 ? v[8] : v[16 - q], v[31 - q]);
-        lo[8 + q] = pick(t0, v[16 + q], v[8 + q]);
-        hi[8 + q] = pick(t0, v[31 - q], v[23 - q]);
+        lo[8 + q] = pick(t0, v[24 + q], v[8 + q]);
+        hi[8 + q] = v[23 - q];
     }
 }
 __device__ __forceinline__ void from_slots(cf (&v)[32], bool t0, const cf (&lo)[16], const cf (&hi)[16])
@@ -329,8 +364,8 @@ __device__ __forceinline__ void from_slots(cf (&v)[32], bool t0, const cf (&lo)[
     for (int q = 0; q < 8; ++q) {
         v[q] = lo[q];
         v[8 + q] = pick(t0, hi[q == 0 ? 0 : 8 - q], lo[8 + q]);
-        v[16 + q] = pick(t0, lo[8 + q], hi[15 - q]);
-        v[24 + q] = pick(t0, hi[15 - q], hi[7 - q]);
+        v[16 + q] = hi[15 - q];
+        v[24 + q] = pick(t0, lo[8 + q], hi[7 - q]);
     }
 }
 

@@ -119,9 +119,9 @@ __global__ void k_line_table(float2* out, int n, int r1)
     double ang, a = 1.0; // the entry is a exp(-i pi ang)
     if (i < n) {
         ang = 2.0 * ((i % T1) * (i / T1) % n) / n;
-    } else if (i < n + n / 2) { // slot q of thread t: k = t + T3 q; thread 0, q >= 8: T3 / 2 + T3 (q - 8)
+    } else if (i < n + n / 2) { // slot q of thread t: k = t + T3 q; thread 0, q >= 8: k = T3 / 2 + T3 q
         const int q = (i - n) / TPL, t = (i - n) % TPL;
-        ang = 0.5 * (T3 * q + (q >= 8 && t == 0 ? T3 / 2 - 8 * T3 : t)) / n;
+        ang = 0.5 * (T3 * q + (q >= 8 && t == 0 ? T3 / 2 : t)) / n;
         a = 0.5 * sqrt(2.0 / n);
     } else if (i < n + n / 2 + T1) {
         const int j = i - n - n / 2;
@@ -224,7 +224,7 @@ int tables_init_device(int device)
     size_t line_entries = 0;
     for (int i = 0; i < kNumLineLens; ++i) {
         t->line_off[i] = (int)line_entries;
-        line_entries += (size_t)line_table_size(256 << i);
+        line_entries += (size_t)line_table_size(32 << i);
     }
     const size_t line_at = off;
     off += align_up(line_entries * sizeof(float2), 256);
@@ -257,7 +257,7 @@ int tables_init_device(int device)
     }
     t->line_tab = reinterpret_cast<float2*>(base + line_at);
     for (int i = 0; i < kNumLineLens; ++i) {
-        const int n = 256 << i, size = line_table_size(n);
+        const int n = 32 << i, size = line_table_size(n);
         k_line_table<<<(size + 255) / 256, 256>>>(t->line_tab + t->line_off[i], n, line_plan(n).r1);
     }
     t->mix_tab = reinterpret_cast<float2*>(base + mix_at);
