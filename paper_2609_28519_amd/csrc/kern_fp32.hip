@@ -13,6 +13,8 @@
 //     a lane transforms a row, the rows meet in an LDS tile, a lane transforms a
 //     column.  Variants stage the tile through LDS with coalesced 16-byte moves and
 //     cap the resident workgroups per CU (fewer bytes in flight per CU).
+//   k_pack (rectangles, rows, cols <= 64): one wavefront per tile of 64 / min(rows, cols)
+//     arrays, a line per lane in both passes.
 //   k_fused (rows, cols <= 128): a workgroup stages a tile of whole arrays in LDS with
 //     a padded row pitch of cols + 4 and runs a row pass and a column pass there.
 //   k_split64 / k_split128 / k_split256: one workgroup per array, each transform shared
@@ -369,6 +371,127 @@ k_wave(Addr a, int64_t batch, const float2* __restrict__ twh_in, const float2* _
             wave_tile_out<H, W>(lds, a, b0, batch, t);
         }
         __syncthreads();
+    }
+}
+
+// Wave-local kernel for rectangles (rows, cols <= 64, rows != cols): one wavefront per tile of
+// 64 / min(rows, cols) arrays, so that the short-axis pass has a line for every lane (k_wave's tile of
+// 64 / max(rows, cols) arrays leaves 56 of 64 lanes idle there for 8 x 64) and the other pass
+// max / min lines per lane, one after another.  The tile enters and leaves LDS by whole-tile coalesced
+// 16-byte moves.
+// Bound: HBM, as for the squares of the longer axis.  Layout: the rows of an array unpadded, the
+// 16-byte groups of row r XOR-permuted by a row key, so that neither the 16-byte accesses of a lane
+// per row nor the 4-byte accesses of a lane per column meet in a bank; narrow arrays are W floats
+// further apart than they are long, so that the columns of several of them spread over the banks.
+template <int H, int W>
+struct PackCfg {
+    static constexpr int A = 64 / (H < W ? H : W);       // arrays per tile
+    static constexpr int G = W / 4, RPL = W >= 32 ? 1 : 32 / W;
+    static constexpr int BS = H * W + (W < 32 && H > W ? W : 0);
+    static constexpr int LDS_FLOATS = A * BS;
+    static constexpr int CPB = H * W / 4, NI = A * CPB / 64; // 16-byte chunks per array, moves per lane
+    static constexpr int RPT = A * H / 64, CPT = A * W / 64; // rows and columns per lane
+    __device__ static int at4(int r, int j) { return r * W + 4 * (j ^ ((r / RPL) & (G - 1))); }
+    __device__ static int at(int r, int c) { return at4(r, c >> 2) + (c & 3); }
+};
+
+template <int H, int W, bool INV>
+__device__ __forceinline__ void pack_rows(float* lds, int t, const float2* tw_in)
+{
+    using C = PackCfg<H, W>;
+#pragma unroll 1
+    for (int i = 0; i < C::RPT; ++i) {
+        const int idx = t + 64 * i, r = idx % H;
+        float* p = lds + idx / H * C::BS;
+        const twptr tw = per_iteration(tw_in);
+        float v[W];
+#pragma unroll
+        for (int j = 0; j < W / 4; ++j) {
+            const float4 q = *reinterpret_cast<const float4*>(p + C::at4(r, j));
+            v[4 * j] = q.x; v[4 * j + 1] = q.y; v[4 * j + 2] = q.z; v[4 * j + 3] = q.w;
+        }
+        if (INV) dct3_ortho<W>(v, tw); else dct2_ortho<W>(v, tw);
+#pragma unroll
+        for (int j = 0; j < W / 4; ++j)
+            *reinterpret_cast<float4*>(p + C::at4(r, j)) = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+    }
+}
+
+template <int H, int W, int DIR>
+__global__ void __launch_bounds__(64)
+k_pack(Addr a, int64_t batch, const float2* __restrict__ twh_in, const float2* __restrict__ tww_in)
+{
+    using C = PackCfg<H, W>;
+    __shared__ float4 lds4[C::LDS_FLOATS / 4];
+    float* lds = reinterpret_cast<float*>(lds4);
+    const int t = threadIdx.x;
+    const int64_t b0 = (int64_t)blockIdx.x * C::A;
+    // chunk 64 i + t of the tile: array and 16-byte chunk of it (a tail slot past the batch transforms a
+    // copy of the tile's first array and is never stored)
+    auto chunk = [&](int i, int& bb, int& q) {
+        const int c = 64 * i + t;
+        bb = C::CPB >= 64 ? 64 * i / C::CPB : c / C::CPB;
+        q = c - bb * C::CPB;
+    };
+    {
+        const gfloat* base = a.src_base();
+        float4 f[C::NI < 8 ? C::NI : 8];
+#pragma unroll
+        for (int g = 0; g < C::NI; g += 8) {
+#pragma unroll
+            for (int i = g; i < g + 8 && i < C::NI; ++i) {
+                int bb, q;
+                chunk(i, bb, q);
+                f[i - g] = *reinterpret_cast<const gfloat4*>(base + a.src_off(b0 + bb < batch ? b0 + bb : b0) + 4 * q);
+            }
+#pragma unroll
+            for (int i = g; i < g + 8 && i < C::NI; ++i) {
+                int bb, q;
+                chunk(i, bb, q);
+                *reinterpret_cast<float4*>(lds + bb * C::BS + C::at4(q / C::G, q % C::G)) = f[i - g];
+            }
+        }
+    }
+    __syncthreads();
+    if (DIR == DCT2D_INVERSE) pack_rows<H, W, true>(lds, t, tww_in); else pack_rows<H, W, false>(lds, t, tww_in);
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < C::CPT; ++i) {
+        const int idx = t + 64 * i, bb = idx / W, c = idx % W;
+        float* p = lds + bb * C::BS;
+        const twptr tw = per_iteration(twh_in);
+        float v[H];
+#pragma unroll
+        for (int r = 0; r < H; ++r) v[r] = p[C::at(r, c)];
+        if constexpr (DIR == DIR_FILTER) filter1d<H>(v, a.lam_for(b0 + bb < batch ? b0 + bb : b0) + c, W, tw);
+        else apply1d<H, DIR>(v, tw);
+#pragma unroll
+        for (int r = 0; r < H; ++r) p[C::at(r, c)] = v[r];
+    }
+    __syncthreads();
+    if (DIR >= DCT2D_ROUNDTRIP) {
+        pack_rows<H, W, true>(lds, t, tww_in);
+        __syncthreads();
+    }
+    gfloat* base = a.dst_base();
+#pragma unroll
+    for (int g = 0; g < C::NI; g += 8) {
+        gfloat* p[8];
+        bool ok[8];
+#pragma unroll
+        for (int i = g; i < g + 8 && i < C::NI; ++i) {
+            int bb, q;
+            chunk(i, bb, q);
+            ok[i - g] = b0 + bb < batch;
+            p[i - g] = base + a.dst_off(ok[i - g] ? b0 + bb : b0) + 4 * q;
+        }
+#pragma unroll
+        for (int i = g; i < g + 8 && i < C::NI; ++i) {
+            int bb, q;
+            chunk(i, bb, q);
+            const float4 v = *reinterpret_cast<const float4*>(lds + bb * C::BS + C::at4(q / C::G, q % C::G));
+            if (ok[i - g]) *reinterpret_cast<gfloat4*>(p[i - g]) = v;
+        }
     }
 }
 
@@ -1480,6 +1603,60 @@ int launch_wave(const DeviceTables* t, const Job& j)
     }
 }
 
+// Variants 13 + k: no more than kPackCaps[k] resident workgroups per CU (0: as many as fit).
+constexpr int kPackCaps[4] = {0, 16, 10, 6};
+
+template <int H, int W, int DIR>
+int launch_pack_dir(const DeviceTables* t, const Job& j)
+{
+    using C = PackCfg<H, W>;
+    const int64_t grid = (j.batch + C::A - 1) / C::A;
+    if (grid > 0x7fffffff) return DCT2D_ERR_ARG;
+    const int cap = kPackCaps[j.variant - 13];
+    const size_t per_wg = cap ? (size_t)(160 * 1024 / cap) & ~(size_t)255 : 0, have = sizeof(float) * C::LDS_FLOATS;
+    k_pack<H, W, DIR><<<(unsigned)grid, 64, per_wg > have ? per_wg - have : 0, j.stream>>>(
+        j.addr(), j.batch, tw_for(t, H), tw_for(t, W));
+    return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
+}
+
+template <int H, int W>
+int launch_pack_hw(const DeviceTables* t, const Job& j)
+{
+    if constexpr (H == W) {
+        return DCT2D_ERR_SIZE;
+    } else {
+        switch (j.dir) {
+        case DCT2D_FORWARD: return launch_pack_dir<H, W, DCT2D_FORWARD>(t, j);
+        case DCT2D_INVERSE: return launch_pack_dir<H, W, DCT2D_INVERSE>(t, j);
+        case DIR_FILTER: return launch_pack_dir<H, W, DIR_FILTER>(t, j);
+        default: return launch_pack_dir<H, W, DCT2D_ROUNDTRIP>(t, j);
+        }
+    }
+}
+
+template <int H>
+int pack_w(const DeviceTables* t, const Job& j)
+{
+    switch (j.cols) {
+    case 8: return launch_pack_hw<H, 8>(t, j);
+    case 16: return launch_pack_hw<H, 16>(t, j);
+    case 32: return launch_pack_hw<H, 32>(t, j);
+    case 64: return launch_pack_hw<H, 64>(t, j);
+    default: return DCT2D_ERR_SIZE;
+    }
+}
+
+int launch_pack(const DeviceTables* t, const Job& j)
+{
+    switch (j.rows) {
+    case 8: return pack_w<8>(t, j);
+    case 16: return pack_w<16>(t, j);
+    case 32: return pack_w<32>(t, j);
+    case 64: return pack_w<64>(t, j);
+    default: return DCT2D_ERR_SIZE;
+    }
+}
+
 template <int DIR, bool STAGE>
 int launch_split128_dir(const DeviceTables* t, const Job& j)
 {
@@ -1687,7 +1864,8 @@ int launch_fused(const DeviceTables* t, const Job& j)
 //                     5..12 as 3 (odd) or 4 (even) with at most 16, 10, 6, 4 resident
 //                     workgroups per CU; 64 x 64 only: 13 split fused (two wavefronts per
 //                     transform, one array per workgroup), 14, 15 as 13 with at most 6, 4
-//                     resident workgroups per CU
+//                     resident workgroups per CU; rectangles: 13..16 k_pack, uncapped and with at most
+//                     16, 10, 6 resident workgroups per CU
 //   128 x 128:        0 split fused (two wavefronts per transform), 1 LDS-staged fused, 2 two-pass,
 //                     3 split fused with the rows (inverse: columns) read through an LDS copy
 //                     of the array, 4 and 5 as 3 and 0 with one array per workgroup
@@ -1713,7 +1891,7 @@ int fp32_tile_variant(int rows, int cols)
 int fp32_variant_count(int rows, int cols, int)
 {
     if (rows == 64 && cols == 64) return 16;
-    if (rows <= 64 && cols <= 64) return 13;
+    if (rows <= 64 && cols <= 64) return rows == cols ? 13 : 17;
     return fp32_tile_variant(rows, cols) + (tile_shape(rows, cols) ? 2 : 0);
 }
 
@@ -1721,8 +1899,7 @@ int fp32_variant_count(int rows, int cols, int)
 // with 512 MiB batches), by the longer axis of arrays up to 64 x 64: 8 staged; 16 staged
 // with at most 16 workgroups per CU; 32 at most 10 per CU, staged for the round trip;
 // 64 x 64 the two-wavefront split kernel, with at most 4 workgroups per CU for forward and
-// inverse.  Rectangles with a longer axis of 32: staged, at most 16 per CU; of 64: staged,
-// uncapped (a short axis leaves most lanes of one pass idle, so more resident tiles pay).  The staged split kernel for 128 x 128 with one array per workgroup; the
+// inverse.  The staged split kernel for 128 x 128 with one array per workgroup; the
 // whole-array register kernel for the other shapes with an axis of 128 or 256 and none below 32.
 int fp32_default_variant(int rows, int cols, int dir)
 {
@@ -1730,7 +1907,15 @@ int fp32_default_variant(int rows, int cols, int dir)
         const int m = rows > cols ? rows : cols;
         const bool rt = dir == DCT2D_ROUNDTRIP;
         if (rows == 64 && cols == 64) return rt ? 13 : 15;
-        if (rows != cols && m >= 32) return m == 32 ? 6 : 4;
+        if (rows != cols) {
+            // k_pack where it leads (8 x 64: 286 / 300 / 421 us with variant 4 against 198 / 198 / 218 with 15 for
+            // forward / inverse / round trip; 16 x 64 round trip 264 / 210; 8 x 32 round trip 249 / 195), else the
+            // wave-local kernel whose lanes are half busy at least
+            const int s = rows < cols ? rows : cols;
+            if (m == 64) return s == 8 || (rt && s == 16) ? 15 : s == 32 && !rt ? 8 : 6;
+            if (m == 32) return s == 8 ? (rt ? 13 : 4) : (rt ? 4 : 6);
+            return rt ? 4 : 14;
+        }
         return m <= 8 ? 4 : m <= 16 ? 6 : m <= 32 ? (rt ? 8 : 7) : (rt ? 4 : 12);
     }
     if (rows == 128 && cols == 128) return 4;
@@ -1770,7 +1955,7 @@ int fp32_unshared_variant(int rows, int cols, int v)
 int launch_fp32(const DeviceTables* t, const Job& j)
 {
     if (j.rows <= 64 && j.cols <= 64) {
-        if (j.variant >= 13) return launch_split64(t, j);
+        if (j.variant >= 13) return j.rows == j.cols ? launch_split64(t, j) : launch_pack(t, j);
         if (j.variant == 0 || j.variant >= 3) return launch_wave(t, j);
         if (j.variant == 1) return launch_fused(t, j);
         return launch_two_pass(t, j);
