@@ -10,7 +10,7 @@
 // (such as 384) without a workspace; axes of any other length get dense float32 Q tables and the
 // class a workspace.  The whole batch is then
 // recorded once into a HIP graph: one fork-join branch per class, so independent
-// classes run concurrently.  Kernels read the batch base pointer from a plan-owned
+// classes run concurrently (a small batch: one class after another).  Kernels read the batch base pointer from a plan-owned
 // device slot, so the recorded graph replays on any buffer.
 //
 // Execute: if the base differs from the one in the slot, one 8-byte copy updates the
@@ -53,6 +53,12 @@ bool long_shape(int r, int c)
 bool image_shape(int r, int c) { return !fast_shape(r, c) && !long_shape(r, c); }
 // an axis that takes a dense product, which cannot run in place
 bool workspace_shape(int r, int c) { return image_shape(r, c) && !(line_axis(r) && line_axis(c)); }
+
+// Batches up to this many floats record their classes one after another.  The branches of a fork cross
+// queues, and a graph of them takes 83 - 105 us to run however little they do; a chain of 8 classes
+// takes 67 us (700 blocks, 1.8 million floats) and 76 (3000 blocks, 6.7 million), but 119 against 92
+// - 109 at 10,000 blocks (25 million), where the branches' work starts to overlap.
+constexpr int64_t kChainFloats = int64_t(1) << 23;
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -129,12 +135,14 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     std::map<std::pair<int, int>, std::vector<int64_t>> groups;
     std::vector<std::pair<int64_t, int64_t>> spans;
     spans.reserve((size_t)count);
+    int64_t floats = 0;
     for (int64_t i = 0; i < count; ++i) {
         const dct2d_block& b = blocks[i];
         if (b.rows < 8 || b.cols < 8 || b.rows > 1024 || b.cols > 1024) return DCT2D_ERR_SIZE;
         if (b.offset < 0 || (b.offset & 3)) return DCT2D_ERR_ALIGN;
         if ((b.cols & 3) != 0) return DCT2D_ERR_SIZE; // rows are read as 16-byte vectors
         groups[{b.rows, b.cols}].push_back(b.offset);
+        floats += (int64_t)b.rows * b.cols;
         spans.push_back({b.offset, b.offset + (int64_t)b.rows * b.cols});
     }
     std::sort(spans.begin(), spans.end());
@@ -219,7 +227,8 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
         release(p);
         return DCT2D_ERR_HIP;
     }
-    // record the graph: fork one branch per class from s0, join back
+    // record the graph: fork one branch per class from s0, join back; a small batch as a chain
+    const bool chain = floats <= kChainFloats;
     const size_t ncls = p->cls.size();
     p->streams.resize(ncls + 1, nullptr);
     p->events.resize(ncls + 1, nullptr);
@@ -237,6 +246,10 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     }
     rc = hipEventRecord(p->events[0], s0) == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
     for (size_t i = 0; i < ncls && rc == DCT2D_OK; ++i) {
+        if (chain) {
+            rc = record_class(t, p, p->cls[i], s0);
+            continue;
+        }
         hipStream_t si = p->streams[i + 1];
         if (hipStreamWaitEvent(si, p->events[0], 0) != hipSuccess) rc = DCT2D_ERR_HIP;
         if (rc == DCT2D_OK) rc = record_class(t, p, p->cls[i], si);
