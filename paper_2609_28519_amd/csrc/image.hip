@@ -4,11 +4,11 @@
 // Shapes whose axes are both powers of two go to the kernels of the basic calls: up to 256
 // the frozen float32-accurate path, with an axis of 512 or 1024 the two-pass line kernels
 // (kern_line.hip).  Every other shape is computed exactly, without zero-padding, axis by axis
-// (launch_image): a power-of-two axis by the line kernels, one whose length has small prime
-// factors (384, 600, 1000) by the mixed-radix kernels (kern_mix.hip), each in place on the output;
-// any other length from the dense Q_n of eq. 1 (FP64-generated, rounded to float32,
-// kern_dense.hip).  A dense pass writes its output tile from whole input rows or columns, so it
-// goes through a workspace of one float32 image per image of the batch.
+// (launch_image): a power-of-two axis by the line kernels, other lengths (384, 600, 1000) by the
+// mixed-radix kernels (kern_mix.hip), each in place on the output; heights
+// p, 2p and 3p with a large prime p from the dense Q_n of eq. 1 (FP64-generated, rounded to float32,
+// kern_dense.hip).  The dense pass writes its output tile from whole input columns, so it goes
+// through a workspace of one float32 image per image of the batch.
 //
 // dct2d_image_transform takes its workspace from the stream-ordered allocator
 // (hipMallocAsync / hipFreeAsync on the caller's stream, so concurrent calls on different
@@ -30,10 +30,10 @@ namespace {
 
 // ---- the no-allocation scratch ---------------------------------------------------------
 // 64 MiB per device, held from the library's load until the process ends.  Layout per
-// call: dense Q_rows, then Q_cols (when cols != rows), then the workspace, each region
-// 256-byte aligned.  The largest dense shape (1024 x 1020) needs 2 x 4 MiB of tables and
-// 4 MiB per image of workspace, so every accepted shape fits at least one image per chunk
-// (power-of-two shapes, 1024 x 1024 included, do not use the scratch).
+// call of a height that takes the dense product: Q_rows, then the workspace, 256-byte
+// aligned.  The largest (1021 x 1024) needs 4 MiB of table and 4 MiB per image of
+// workspace, so every accepted shape fits at least one image per chunk (other shapes do not
+// use the scratch).
 constexpr size_t kScratchBytes = size_t(64) << 20;
 __device__ __align__(256) float scratch[kScratchBytes / sizeof(float)];
 
@@ -118,43 +118,31 @@ float* scratch_ptr(int* err)
 
 } // namespace
 
-int dct::launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows, const float* q_cols)
+int dct::launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows)
 {
     const int64_t n = (int64_t)j.rows * j.cols;
     const Addr in = j.addr();
     const Addr out{j.out, j.out, j.out_stride, j.out_stride, j.out_idx, j.out_idx, j.out_slot, j.out_slot};
-    const Addr in_ws{j.in, ws, j.in_stride, n, j.in_idx, nullptr, j.in_slot, nullptr};
-    const Addr ws_out{ws, j.out, n, j.out_stride, nullptr, j.out_idx, nullptr, j.out_slot};
-    const Addr out_ws{j.out, ws, j.out_stride, n, j.out_idx, nullptr, j.out_slot, nullptr};
-    const bool row_line = line_axis(j.cols), col_line = line_axis(j.rows);
     auto line = [&](const Addr& a, bool column_pass) {
         return launch_line_axis(t, a, j.batch, j.rows, j.cols, column_pass, j.dir, j.stream);
     };
-    auto dense = [&](const Addr& a, bool column_pass, bool inverse) {
-        return launch_dense_axis(a, j.batch, j.rows, j.cols, column_pass, inverse, column_pass ? q_rows : q_cols,
-                                 j.stream);
-    };
-    int rc;
-    if (row_line && col_line) {
-        rc = line(in, false);
+    if (line_axis(j.rows)) {
+        const int rc = line(in, false);
         return rc == DCT2D_OK ? line(out, true) : rc;
     }
-    const bool inv = j.dir == DCT2D_INVERSE;
+    const Addr in_ws{j.in, ws, j.in_stride, n, j.in_idx, nullptr, j.in_slot, nullptr};
+    const Addr ws_out{ws, j.out, n, j.out_stride, nullptr, j.out_idx, nullptr, j.out_slot};
+    auto dense = [&](const Addr& a, bool inverse) {
+        return launch_dense_columns(a, j.batch, j.rows, j.cols, inverse, q_rows, j.stream);
+    };
     if (j.dir != DCT2D_ROUNDTRIP) {
-        rc = row_line ? line(in_ws, false) : dense(in_ws, false, inv);
-        if (rc != DCT2D_OK) return rc;
-        return col_line ? line(ws_out, true) : dense(ws_out, true, inv);
+        const int rc = line(in_ws, false);
+        return rc == DCT2D_OK ? dense(ws_out, j.dir == DCT2D_INVERSE) : rc;
     }
-    // round trip: the axes commute (Q_h^T Q_h X Q_w^T Q_w); a line axis is one in-place pass
-    const bool cols_first = !col_line;
-    rc = dense(in_ws, cols_first, false);
-    if (row_line || col_line) {
-        if (rc == DCT2D_OK) rc = dense(ws_out, cols_first, true);
-        return rc == DCT2D_OK ? line(out, col_line) : rc;
-    }
-    if (rc == DCT2D_OK) rc = dense(ws_out, false, false);
-    if (rc == DCT2D_OK) rc = dense(out_ws, false, true);
-    return rc == DCT2D_OK ? dense(ws_out, true, true) : rc;
+    // round trip: the axes commute (Q_h^T Q_h X Q_w^T Q_w), the rows are one in-place pass
+    int rc = dense(in_ws, false);
+    if (rc == DCT2D_OK) rc = dense(ws_out, true);
+    return rc == DCT2D_OK ? line(out, false) : rc;
 }
 
 int dct::image_scratch_init(int device)
@@ -206,11 +194,9 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
         return launch_long(t, j);
     }
     Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
-    const bool row_line = line_axis(cols), col_line = line_axis(rows);
-    if (row_line && col_line) return launch_image(t, j, nullptr, nullptr, nullptr);
-    const float *q_rows = nullptr, *q_cols = nullptr;
-    if (!col_line && !(q_rows = cached_q(t->device, rows, &rc))) return rc;
-    if (!row_line && !(q_cols = cached_q(t->device, cols, &rc))) return rc;
+    if (line_axis(rows)) return launch_image(t, j, nullptr, nullptr);
+    const float* q_rows = cached_q(t->device, rows, &rc);
+    if (!q_rows) return rc;
     const int64_t n = (int64_t)rows * cols;
     const int64_t per = batch < 65535 ? batch : 65535; // the dense grid's z extent
     float* ws = nullptr;
@@ -220,7 +206,7 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
         j.batch = batch - b0 < per ? batch - b0 : per;
         j.in = in + b0 * in_stride;
         j.out = out + b0 * out_stride;
-        rc = launch_image(t, j, ws, q_rows, q_cols);
+        rc = launch_image(t, j, ws, q_rows);
     }
     if (hipFreeAsync(ws, s) != hipSuccess && rc == DCT2D_OK) rc = DCT2D_ERR_HIP;
     return rc;
@@ -244,29 +230,25 @@ int dct2d_image_transform_noalloc(int dir, const float* in, float* out, int64_t 
         return launch_long(t, j);
     }
     Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
-    const bool row_line = line_axis(cols), col_line = line_axis(rows);
-    if (row_line && col_line) return launch_image(t, j, nullptr, nullptr, nullptr);
+    if (line_axis(rows)) return launch_image(t, j, nullptr, nullptr);
     float* base = scratch_ptr(&rc);
     if (!base) return rc;
     const size_t n = (size_t)rows * cols;
-    const size_t q_cols_off = col_line || rows == cols ? 0 : align256((size_t)rows * rows * sizeof(float));
-    const size_t ws_off = row_line ? q_cols_off : align256(q_cols_off + (size_t)cols * cols * sizeof(float));
+    const size_t ws_off = align256((size_t)rows * rows * sizeof(float));
     if (ws_off + n * sizeof(float) > kScratchBytes) return DCT2D_ERR_SIZE; // not reached for accepted shapes
     const int64_t fit = (int64_t)((kScratchBytes - ws_off) / (n * sizeof(float)));
     const int64_t per = fit < 65535 ? fit : 65535;
     char* b = reinterpret_cast<char*>(base);
     float* q_rows = reinterpret_cast<float*>(b);
-    float* q_cols = reinterpret_cast<float*>(b + q_cols_off);
     float* ws = reinterpret_cast<float*>(b + ws_off);
-    // the tables are rebuilt on the caller's stream every call: the scratch keeps whatever
-    // the previous call on this device left in it
-    if (!col_line) rc = tables_dense_q(rows, q_rows, s);
-    if (rc == DCT2D_OK && !row_line && cols != rows) rc = tables_dense_q(cols, q_cols, s);
+    // the table is rebuilt on the caller's stream every call: the scratch keeps whatever the previous
+    // call on this device left in it
+    rc = tables_dense_q(rows, q_rows, s);
     for (int64_t b0 = 0; b0 < batch && rc == DCT2D_OK; b0 += per) {
         j.batch = batch - b0 < per ? batch - b0 : per;
         j.in = in + b0 * in_stride;
         j.out = out + b0 * out_stride;
-        rc = launch_image(t, j, ws, q_rows, q_cols);
+        rc = launch_image(t, j, ws, q_rows);
     }
     return rc;
 }

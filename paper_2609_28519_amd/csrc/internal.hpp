@@ -24,6 +24,7 @@ struct DeviceTables {
     float2* line_tab = nullptr;         // tables of the line-pair transforms (line_fft.hpp)
     int line_off[kNumLineLens] = {};    // offset per length, 32 << i
     float2* mix_tab = nullptr;          // tables of the mixed-radix transforms, every length (mix_fft.hpp)
+    float2* prime_tab = nullptr;        // factors of the large prime radices (mix_fft.hpp)
     // Dense Q_n for the matrix paths, row-major n x n, for n = 8 << i:
     float* q_f32[kNumDense] = {};       // rounded to float32
     uint16_t* q_bf16[kNumDense] = {};   // 3 planes: hi, mid, lo (bf16 bit patterns)
@@ -171,10 +172,9 @@ struct Job {
 // kernel variant, then launches.  Shared by the basic calls and ragged plans.
 int dispatch(const DeviceTables* t, Job j, int precision);
 
-// Dense axis pass (kern_dense.hip): one length-L transform along the columns
-// (column_pass) or rows of `count` row-major images, through a dense float32 Q_L.
-int launch_dense_axis(const Addr& a, int64_t count, int rows, int cols, bool column_pass, bool inverse,
-                      const float* q, hipStream_t s);
+// Dense column pass (kern_dense.hip): the transform of length `rows` along the columns of `count`
+// row-major images, through a dense float32 Q_rows; a.src and a.dst must not overlap.
+int launch_dense_columns(const Addr& a, int64_t count, int rows, int cols, bool inverse, const float* q, hipStream_t s);
 
 int launch_fp32(const DeviceTables* t, const Job& j);
 // One pass of direction `dir` along the rows (or, column_pass, the columns) of length
@@ -185,18 +185,19 @@ int launch_short_line_pass(const DeviceTables* t, const Addr& a, int64_t batch, 
 // pass and a column pass, the second in place on the output.
 int launch_long(const DeviceTables* t, const Job& j);
 // A pass of direction `dir` along the rows or the columns of rows x cols arrays (cols a multiple of
-// 4), whose length has small prime factors only (mix_smooth), in place or not (kern_mix.hip).
+// 4) of a length that mix_plan admits (mix_smooth), in place or not (kern_mix.hip).
 bool mix_smooth(int n);
 int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass, int dir,
                     hipStream_t s);
 // The same along an axis of any length that transforms its lines in place: powers of two and
-// lengths with small prime factors (line_axis).
+// the lengths that mix_smooth admits (line_axis).
 bool line_axis(int n);
 int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass,
                      int dir, hipStream_t s);
-// Whole images (both axes in [8, 1024], not both powers of two).  Axes outside line_axis take a dense
-// product: they need the length's Q and a workspace of rows * cols floats per image.
-int launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows, const float* q_cols);
+// Whole images (both axes in [8, 1024], not both powers of two, cols a multiple of 4, which makes it a
+// line_axis).  Rows outside line_axis take a dense product: it needs Q_rows and a workspace of
+// rows * cols floats per image.
+int launch_image(const DeviceTables* t, const Job& j, float* ws, const float* q_rows);
 // Rectangles with one axis of 256 and the other at most 128, fused (kern_rect256.hip).
 int launch_rect256(const DeviceTables* t, const Job& j);
 // One array per workgroup in registers, both axes 32 .. 256 and one of 128 or 256 (kern_tile.hip).

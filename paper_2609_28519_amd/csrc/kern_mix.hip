@@ -1,7 +1,7 @@
-// Axes whose length is not a power of two but has small prime factors, 8 .. 1024 (image axes such as
-// 384, 600, 720, 1000; also 256 .. 1024 in images with an odd number of rows): one pass over HBM per
-// axis, in place or not, each line pair transformed by a mixed-radix DFT in LDS (mix_fft.hpp).  No
-// workspace and no dense table.
+// Axes whose length is not a power of two, 8 .. 1024 (image axes such as 384, 600, 720, 1000; also
+// 256 .. 1024 in images with an odd number of rows), all but p, 2p and 3p with a large prime p (mix_plan):
+// one pass over HBM per axis, in place or not, each line pair transformed by a mixed-radix DFT in LDS
+// (mix_fft.hpp).  No workspace and no dense table.
 //
 // A workgroup holds 8 or more pairs (16 values per thread), the pairs fastest in LDS, so that every
 // pass reads and writes it without bank conflicts whatever the radices; twiddles come from an LDS copy
@@ -14,7 +14,12 @@
 // 2^25 floats, out of place, us, the dense products before -> now (forward / round trip):
 //   512 x 384  400 -> 140, 727 -> 190     600 x 1000  705 -> 186, 1287 -> 291
 //   768 x 768  619 -> 161, 1124 -> 247    720 x 480   570 -> 179, 1038 -> 269
+// With a large prime factor the prime's pass is bound by the vector ALU, about R multiply-adds per
+// complex value; 10^7 floats, forward: 822 x 712 (137, 89) 583 -> 168 us, 1004 x 1004 (251) 807 -> 349,
+// 961 x 1020 (31, 17) 821 -> 87.
 #include <hip/hip_runtime.h>
+
+#include <array>
 
 #include "internal.hpp"
 #include "mix_fft.hpp"
@@ -33,6 +38,8 @@ struct MixArgs {
     int lines;          // lines per array
     int es, ls;         // element and line stride
     const float2* tab;
+    const float2* prime;       // factors of the large prime radices
+    int prime_at[kMixStages];  // where those of each stage's begin
 };
 
 // LDS: the table (W, then c) from byte 0, then value e of slot l at (e * SLOTS + l).
@@ -88,42 +95,87 @@ __device__ __forceinline__ void mix_pass(uint32_t zb, const MixArgs& g, int stag
     mix_sync();
 }
 
-// A prime radix without a code of its own: each output is a sum over its butterfly's inputs.
+// A prime radix without a code of its own, R = 2 H + 1: with t_j = x_j + x_{R-j}, d_j = x_j - x_{R-j},
+//   X_k, X_{R-k} = (x_0 + sum_j cos(2 pi jk / R) t_j) -+ i sum_j sin(2 pi jk / R) d_j,   k <= H.
+// A lane has one butterfly, a wavefront kPrimeBlock values of k for 64 butterflies: the factors are
+// the same in every lane (scalar loads from the prime's table), and one pair of LDS reads serves 4
+// kPrimeBlock multiply-adds.  Outputs wait in registers until every wavefront has read its inputs;
+// mix_plan admits lengths whose wavefronts then have at most two such tasks each.
 template <int SLOTS, int NT>
-__device__ __forceinline__ void mix_pass_any(uint32_t zb, const MixArgs& g, int stage, int tid)
+__device__ __forceinline__ void mix_pass_prime(uint32_t zb, const MixArgs& g, int stage, int tid)
 {
-    const int n = g.plan.n, R = g.plan.radix[stage], m = n / R, s = g.plan.s[stage], total = SLOTS * n;
-    const float inv_m = 1.0f / m;
-    const uint32_t in_step = (uint32_t)(m * SLOTS * 8);
-    cf acc[16];
-    uint32_t in[16];
-    int p[16], e[16];
+    constexpr int KB = kPrimeBlock, NW = NT / 64;
+    const int n = g.plan.n, R = g.plan.radix[stage], H = R / 2, m = n / R, s = g.plan.s[stage], total = SLOTS * m;
+    const uint32_t step = (uint32_t)(m * SLOTS * 8);
+    const int groups = (total + 63) / 64, tasks = groups * ((H + KB) / KB);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    cf lo[2][KB], hi[2][KB];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int idx = tid + NT * i, o = idx / SLOTS;
-        acc[i] = {0.f, 0.f};
-        e[i] = 0;
-        p[i] = idx < total ? mix::div(o, inv_m) : 0;
-        in[i] = zb + 8u * (uint32_t)((o - p[i] * m) * SLOTS + idx % SLOTS);
-        if (idx >= total) in[i] = zb;
-    }
-    for (int r = 0; r < R; ++r) {
+    for (int w = 0; w < 2; ++w) {
+        const int task = wave + NW * w;
+        if (task < tasks) {
+            const int blk = task / groups, b0 = (task - blk * groups) * 64 + lane, b = b0 < total ? b0 : total - 1;
+            uint32_t o1 = zb + (uint32_t)b * 8u, o2 = o1 + (uint32_t)R * step;
+            twptr f = (twptr)g.prime + g.prime_at[stage] + blk * H * KB;
+            const float2 x0 = lds2(o1);
+            cf ca[KB], sb[KB];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float2 x = lds2(in[i] + r * in_step);
-            acc[i] = cadd(acc[i], cmul({x.x, x.y}, lds2(8u * (uint32_t)(m * e[i]))));
-            e[i] += p[i];
-            if (e[i] >= R) e[i] -= R;
+            for (int k = 0; k < KB; ++k) {
+                ca[k] = {x0.x, x0.y};
+                sb[k] = {0.f, 0.f};
+            }
+            // sums of 16 terms, then the sum of those: half the rounding error of one long sum at R = 251
+            for (int j0 = 0; j0 < H; j0 += 16) {
+                cf pc[KB], ps[KB];
+#pragma unroll
+                for (int k = 0; k < KB; ++k) pc[k] = ps[k] = {0.f, 0.f};
+                const int end = H - j0 < 16 ? H - j0 : 16;
+#pragma unroll 2
+                for (int j = 0; j < end; ++j) {
+                    o1 += step;
+                    o2 -= step;
+                    const float2 x1 = lds2(o1), x2 = lds2(o2);
+                    const cf t = {x1.x + x2.x, x1.y + x2.y}, d = {x1.x - x2.x, x1.y - x2.y};
+#pragma unroll
+                    for (int k = 0; k < KB; ++k) {
+                        const float2 c = f[k];
+                        pc[k] = {pc[k].x + c.x * t.x, pc[k].y + c.x * t.y};
+                        ps[k] = {ps[k].x + c.y * d.x, ps[k].y + c.y * d.y};
+                    }
+                    f += KB;
+                }
+#pragma unroll
+                for (int k = 0; k < KB; ++k) {
+                    ca[k] = cadd(ca[k], pc[k]);
+                    sb[k] = cadd(sb[k], ps[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                lo[w][k] = {ca[k].x + sb[k].y, ca[k].y - sb[k].x};
+                hi[w][k] = {ca[k].x - sb[k].y, ca[k].y + sb[k].x};
+            }
         }
     }
     mix_sync();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int idx = tid + NT * i;
-        if (idx < total) {
-            const int u = idx / SLOTS - p[i] * m, sj = s * mix::div(u, g.plan.inv_s[stage]);
-            const cf f = cmul(acc[i], lds2(8u * (uint32_t)(sj * p[i])));
-            lds2(zb + 8u * (uint32_t)((u + sj * (R - 1) + s * p[i]) * SLOTS + idx % SLOTS)) = make_float2(f.x, f.y);
+    for (int w = 0; w < 2; ++w) {
+        const int task = wave + NW * w;
+        if (task < tasks) {
+            const int blk = task / groups, b = (task - blk * groups) * 64 + lane;
+            if (b < total) {
+                const int u = b / SLOTS, sj = s * mix::div(u, g.plan.inv_s[stage]);
+                auto put = [&](cf x, int k) {
+                    const cf y = cmul(x, lds2(8u * (uint32_t)(sj * k)));
+                    lds2(zb + 8u * (uint32_t)((u + sj * (R - 1) + s * k) * SLOTS + b % SLOTS)) = make_float2(y.x, y.y);
+                };
+#pragma unroll
+                for (int i = 0; i < KB; ++i) {
+                    const int k = blk * KB + i;
+                    if (k <= H) put(lo[w][i], k);
+                    if (k > 0 && k <= H) put(hi[w][i], R - k);
+                }
+            }
         }
     }
     mix_sync();
@@ -147,7 +199,7 @@ __device__ __forceinline__ void mix_dft(uint32_t zb, const MixArgs& g)
         case 11: mix_pass<11, SLOTS, NT>(zb, g, st, tid); break;
         case 13: mix_pass<13, SLOTS, NT>(zb, g, st, tid); break;
         case 16: mix_pass<16, SLOTS, NT>(zb, g, st, tid); break;
-        default: mix_pass_any<SLOTS, NT>(zb, g, st, tid); break;
+        default: mix_pass_prime<SLOTS, NT>(zb, g, st, tid); break;
         }
     }
 }
@@ -320,22 +372,29 @@ int mix_run(const MixArgs& g, int dir, hipStream_t s)
     return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
 }
 
-// Pairs per workgroup: as many as 16 values per thread hold, a power of two.  256 threads where 8 pairs
-// (16 columns, 64 bytes of a row) fit them, else 512 (4 pairs at n > 512: 1000 x 600 3 % slower, 768 x 768
-// 2 % faster; 16 pairs of 257 .. 512 in 512 threads: 384 x 384 round trip 246 us against 237).
 template <bool COLS>
 int mix_slots(const MixArgs& g, int dir, hipStream_t s)
 {
-    const int n = g.plan.n;
-    if (n > 512) return mix_run<COLS, 8, 512>(g, dir, s);
-    if (n > 256) return mix_run<COLS, 8, 256>(g, dir, s);
-    if (n > 128) return mix_run<COLS, 16, 256>(g, dir, s);
-    if (n > 32) return mix_run<COLS, 32, 256>(g, dir, s);
-    if (n > 16) return mix_run<COLS, 128, 256>(g, dir, s);
-    return mix_run<COLS, 256, 256>(g, dir, s);
+    switch (mix_shape(g.plan.n).slots) {
+    case 8: return g.plan.n > 512 ? mix_run<COLS, 8, 512>(g, dir, s) : mix_run<COLS, 8, 256>(g, dir, s);
+    case 16: return mix_run<COLS, 16, 256>(g, dir, s);
+    case 32: return mix_run<COLS, 32, 256>(g, dir, s);
+    case 128: return mix_run<COLS, 128, 256>(g, dir, s);
+    default: return mix_run<COLS, 256, 256>(g, dir, s);
+    }
 }
 
 } // namespace
+
+static int prime_offset(int p)
+{
+    static const auto at = [] {
+        std::array<int, kMaxPrime + 1> o{};
+        for (int q = kMixRadix + 1; q < kMaxPrime; ++q) o[q + 1] = o[q] + (is_prime(q) ? prime_table_size(q) : 0);
+        return o;
+    }();
+    return at[p];
+}
 
 bool mix_smooth(int n)
 {
@@ -354,6 +413,9 @@ int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int row
     g.es = column_pass ? cols : 1;
     g.ls = column_pass ? 1 : cols;
     g.tab = t->mix_tab + mix_table_offset(n);
+    g.prime = t->prime_tab;
+    for (int i = 0; i < g.plan.stages; ++i)
+        if (g.plan.radix[i] > 16) g.prime_at[i] = prime_offset(g.plan.radix[i]);
     g.per_array = (uint32_t)((g.lines + 1) / 2);
     const int64_t total = batch * g.per_array;
     if (total > 0x7fffffff) return DCT2D_ERR_ARG;

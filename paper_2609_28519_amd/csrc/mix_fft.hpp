@@ -5,7 +5,7 @@
 // x[2n+1]).  The DFT runs as autosorting passes over LDS: with s the product of the radices done
 // and u = k + s j (k < s, j < N / (R s)), a pass of radix R reads z[u + (N/R) r], r < R, and writes
 //   (DFT_R)_p W_N^{s j p}  to  u + s j (R - 1) + s p.
-// Radices 16, 8, 4, 2, 3, 5, 7, 11, 13 are straight-line codes; a larger prime takes a plain sum.
+// Radices 16, 8, 4, 2, 3, 5, 7, 11, 13 are straight-line codes; a larger prime takes sums over its half length.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -14,11 +14,39 @@
 namespace dct {
 
 constexpr int kMixStages = 8; // a length up to 1024 takes at most 6 (729 = 3^6)
-// Largest prime factor that takes the mixed-radix path, and the largest with a straight-line code.
-// A prime between the two is a plain sum of that many terms per output, worth it on long axes only
-// (n >= 8 times the prime: 1020 = 60 * 17 takes 65 us against 346 for the dense product in 1020 x 700
-// images, but 29 alone lost to it).
-constexpr int kMixPrime = 23, kMixRadix = 13;
+constexpr int kMixRadix = 13; // largest prime with a straight-line code
+
+// Pairs and threads per workgroup for a length: as many pairs as 16 values per thread hold, a power of
+// two.  256 threads where 8 pairs (16 columns, 64 bytes of a row) fit them, else 512 (4 pairs at n > 512:
+// 1000 x 600 3 % slower, 768 x 768 2 % faster; 16 pairs of 257 .. 512 in 512 threads: 384 x 384 round
+// trip 246 us against 237).
+struct MixShape {
+    int slots, threads;
+};
+constexpr MixShape mix_shape(int n)
+{
+    return n > 512 ? MixShape{8, 512} : n > 256 ? MixShape{8, 256} : n > 128 ? MixShape{16, 256}
+         : n > 32 ? MixShape{32, 256} : n > 16 ? MixShape{128, 256} : MixShape{256, 256};
+}
+
+// Larger primes p: tables of the factors cos, sin(2 pi jk / p) in blocks of kPrimeBlock values of k,
+// (cos, sin) of block b, j = 1 .. H, k = b kPrimeBlock + i at (b H + j - 1) kPrimeBlock + i (zeros past
+// k = H = (p - 1) / 2), for p = kMixRadix + 4 .. kMaxPrime (1004 = 4 * 251), one after another.
+constexpr int kPrimeBlock = 8, kMaxPrime = 251;
+constexpr bool is_prime(int p)
+{
+    for (int f = 2; f * f <= p; ++f)
+        if (p % f == 0) return false;
+    return p > 1;
+}
+constexpr int prime_table_size(int p) { return (p / 2 + kPrimeBlock) / kPrimeBlock * (p / 2) * kPrimeBlock; }
+constexpr int prime_table_offset(int p)
+{
+    int o = 0;
+    for (int q = kMixRadix + 1; q < p; ++q)
+        if (is_prime(q)) o += prime_table_size(q);
+    return o;
+}
 
 struct MixPlan {
     int n = 0, stages = 0;
@@ -28,22 +56,22 @@ struct MixPlan {
 };
 
 // The radices of n: odd ones first (their strided writes touch all LDS banks), the largest power of
-// two last (its writes are contiguous).  False if n has a prime factor above kMixPrime.
+// two last (its writes are contiguous).  False for lengths left to the dense products: those with a
+// prime factor so large that fewer than 32 butterflies (of the workgroup's pairs) share it, that is
+// p, 2p and 3p on the longest axes, where most lanes of the prime's pass would idle.
 inline bool mix_plan(int n, MixPlan& p)
 {
     p = MixPlan{};
     p.n = n;
-    int m = n, odd[kMixStages * 2], no = 0;
-    for (int f = 3; f <= kMixPrime; f += 2)
-        while (m % f == 0) {
-            if (f > kMixRadix && n < 8 * f) return false;
+    int q = n, lg = 0, odd[kMixStages], no = 0;
+    for (; q % 2 == 0; q /= 2) ++lg;
+    for (int f = 3; q > 1; f = f * f > q ? q : f + 2) // what is left once f * f > q is prime
+        while (q % f == 0) {
+            if (f > kMixRadix && n / f * mix_shape(n).slots < 32) return false;
             odd[no++] = f;
-            m /= f;
+            q /= f;
         }
-    if (m & (m - 1)) return false;
     for (int i = no - 1; i >= 0; --i) p.radix[p.stages++] = odd[i];
-    int lg = 0;
-    while ((1 << lg) < m) ++lg;
     // 2^lg in the fewest passes of at most 4 bits, the larger ones last
     const int passes = (lg + 3) / 4;
     for (int i = 0; i < passes; ++i) p.radix[p.stages++] = 1 << (lg / passes + (i >= passes - lg % passes ? 1 : 0));

@@ -6,9 +6,8 @@
 // configuration of the frozen per-size policy (the same table the autotuner fills for
 // the basic calls, Section 3.2: variants fixed before measurement), with grid-stride
 // schedules replaced by one tile per workgroup, since the classes share the GPU.  Image classes
-// run pass by pass in place on the batch, power-of-two axes and axes with small prime factors
-// (such as 384) without a workspace; axes of any other length get dense float32 Q tables and the
-// class a workspace.  The whole batch is then
+// run pass by pass in place on the batch, without a workspace; the few lengths that take dense
+// products (line_axis) get float32 Q tables, and their class a workspace.  The whole batch is then
 // recorded once into a HIP graph: one fork-join branch per class, so independent
 // classes run concurrently (a small batch: one class after another).  Kernels read the batch base pointer from a plan-owned
 // device slot, so the recorded graph replays on any buffer.
@@ -36,7 +35,6 @@ struct ClassRec {
     bool image = false;       // an axis that is not a power of two (launch_image)
     bool long_axes = false;   // two-pass long-axis kernels (an axis of 512 or 1024)
     float* q_rows = nullptr;  // dense Q_rows (column pass)
-    float* q_cols = nullptr;  // dense Q_cols (row pass)
     float* ws = nullptr;      // workspace, count * rows * cols floats
 };
 
@@ -51,8 +49,8 @@ bool long_shape(int r, int c)
 }
 
 bool image_shape(int r, int c) { return !fast_shape(r, c) && !long_shape(r, c); }
-// an axis that takes a dense product, which cannot run in place
-bool workspace_shape(int r, int c) { return image_shape(r, c) && !(line_axis(r) && line_axis(c)); }
+// a height that takes the dense product, which cannot run in place
+bool workspace_shape(int r, int c) { return image_shape(r, c) && !line_axis(r); }
 
 // Batches up to this many floats record their classes one after another.  The branches of a fork cross
 // queues, and a graph of them takes 83 - 105 us to run however little they do; a chain of 8 classes
@@ -115,7 +113,7 @@ int record_class(const DeviceTables* t, dct2d_ragged_plan* p, const ClassRec& c,
     Job j{p->dir, nullptr, nullptr, c.count, c.rows, c.cols, 0, 0, s, 0};
     j.in_idx = j.out_idx = c.d_off;
     j.in_slot = j.out_slot = p->d_slot;
-    return launch_image(t, j, c.ws, c.q_rows, c.q_cols);
+    return launch_image(t, j, c.ws, c.q_rows);
 }
 
 } // namespace
@@ -170,11 +168,11 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     for (auto& g : groups) bytes = align256(bytes + g.second.size() * sizeof(int64_t));
     for (auto& g : groups) {
         if (!image_shape(g.first.first, g.first.second)) continue;
-        for (int L : {g.first.first, g.first.second})
-            if (!line_axis(L) && !qoff.count(L)) {
-                qoff[L] = bytes;
-                bytes = align256(bytes + (size_t)L * L * 4);
-            }
+        const int L = g.first.first;
+        if (!line_axis(L) && !qoff.count(L)) {
+            qoff[L] = bytes;
+            bytes = align256(bytes + (size_t)L * L * 4);
+        }
     }
     std::vector<size_t> wsoff;
     for (auto& g : groups) {
@@ -209,9 +207,10 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
         c.long_axes = long_shape(c.rows, c.cols);
         if (image_shape(c.rows, c.cols)) {
             c.image = true;
-            if (!line_axis(c.rows)) c.q_rows = reinterpret_cast<float*>(base + qoff[c.rows]);
-            if (!line_axis(c.cols)) c.q_cols = reinterpret_cast<float*>(base + qoff[c.cols]);
-            if (workspace_shape(c.rows, c.cols)) c.ws = reinterpret_cast<float*>(base + wsoff[gi]);
+            if (workspace_shape(c.rows, c.cols)) {
+                c.q_rows = reinterpret_cast<float*>(base + qoff[c.rows]);
+                c.ws = reinterpret_cast<float*>(base + wsoff[gi]);
+            }
         }
         p->cls.push_back(c);
         ++gi;

@@ -148,6 +148,17 @@ __global__ void k_mix_tables(float2* out)
     }
 }
 
+// Factors of the prime radix p at out (layout in mix_fft.hpp).
+__global__ void k_prime_table(float2* out, int p)
+{
+    const int H = p / 2, i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= prime_table_size(p)) return;
+    const int k = i / (H * kPrimeBlock) * kPrimeBlock + i % kPrimeBlock, j = i / kPrimeBlock % H + 1;
+    double s, c;
+    sincospi(2.0 * (j * k % p) / p, &s, &c);
+    out[i] = k <= H ? make_float2((float)c, (float)s) : make_float2(0.f, 0.f);
+}
+
 __device__ double q_entry(int n, int k, int j)
 {
     const double a = k == 0 ? sqrt(1.0 / n) : sqrt(2.0 / n);
@@ -230,6 +241,8 @@ int tables_init_device(int device)
     off += align_up(line_entries * sizeof(float2), 256);
     const size_t mix_at = off;
     off += align_up((size_t)mix_table_offset(1025) * sizeof(float2), 256);
+    const size_t prime_at = off;
+    off += align_up((size_t)prime_table_offset(kMaxPrime + 1) * sizeof(float2), 256);
     size_t dense_off[kNumDense][7];
     for (int i = 0; i < kNumDense; ++i) {
         const size_t nn = (size_t)(8 << i) * (8 << i);
@@ -262,6 +275,10 @@ int tables_init_device(int device)
     }
     t->mix_tab = reinterpret_cast<float2*>(base + mix_at);
     k_mix_tables<<<1017, 256>>>(t->mix_tab);
+    t->prime_tab = reinterpret_cast<float2*>(base + prime_at);
+    for (int p = kMixRadix + 1; p <= kMaxPrime; ++p)
+        if (is_prime(p))
+            k_prime_table<<<(prime_table_size(p) + 255) / 256, 256>>>(t->prime_tab + prime_table_offset(p), p);
     for (int i = 0; i < kNumDense; ++i) {
         const int n = 8 << i;
         t->q_f32[i] = reinterpret_cast<float*>(base + dense_off[i][0]);
