@@ -716,6 +716,15 @@ __device__ __forceinline__ void tile_products(f32x16& acc, const V (&av)[3][2], 
         }
 }
 
+// Blocks enter and leave through a wavefront's staging area by whole 1 KB moves.  Read and written in
+// the operand layout itself (16 bytes of 32 rows per instruction) the kernel was bound by those
+// accesses whatever its arithmetic: us per 2^27 floats, forward / inverse, before -> now: bf16
+// 289/289 -> 210/208, fp16x3 265/256 -> 223/219, bf16x3 253/239 -> 221/216, fp8 249/247 -> 214/211, bf16x6
+// 300/267 -> 287/249 (192 matrix instructions and 1000 conversions per block bound that one).
+// The staging area: half a block, 32 rows of 64, the 16-byte groups of row r XOR-permuted
+// by r mod 8 (both the row-wise and the lane-per-row accesses then touch every bank).
+__device__ __forceinline__ int stage64(int r, int group) { return r * 64 + 4 * (group ^ (r & 7)); }
+
 // Two workgroups per CU (at most 256 registers per lane, the accumulators included) where
 // the kernel fits them without spilling; the three-part round trip keeps one.
 template <int MODE, int DIR>
@@ -725,6 +734,8 @@ k_mfma64(Addr a, int64_t batch, QTab q)
     constexpr int T0 = ModeInfo<MODE>::target;
     constexpr int NDIR = DIR == DCT2D_ROUNDTRIP ? 2 : 1;
     __shared__ uint4 bl[NDIR * kB64Ops * 64];
+    __shared__ float4 stage[4][512];
+    float* wl = reinterpret_cast<float*>(stage[threadIdx.x >> 6]);
     fill_b64<MODE>(bl, q, NDIR, DIR == DCT2D_INVERSE);
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -735,20 +746,34 @@ k_mfma64(Addr a, int64_t batch, QTab q)
     using V = typename std::conditional<ModeInfo<MODE>::f16, f16x8, bf16x8>::type;
     using E = typename std::conditional<ModeInfo<MODE>::f16, _Float16, __bf16>::type;
     for (int64_t b = wave; b < batch; b += nwaves) {
-        // d[I][K][16]: lane (h, c) holds row 32 I + c, columns 32 K + 8 qq + 4 h .. +3
-        float d[2][2][16];
+        // chunk 64 i + lane of the block: row 4 i + lane / 16, 16-byte group lane % 16
+        float4 g0[8], g1[8];
         const gfloat* src = a.src(b);
 #pragma unroll
-        for (int I = 0; I < 2; ++I)
+        for (int i = 0; i < 8; ++i) g0[i] = *reinterpret_cast<const gfloat4*>(src + 4 * (64 * i + lane));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) g1[i] = *reinterpret_cast<const gfloat4*>(src + 4 * (64 * (8 + i) + lane));
+        // d[I][K][16]: lane (h, c) holds row 32 I + c, columns 32 K + 8 qq + 4 h .. +3
+        float d[2][2][16];
+        auto half = [&](const float4 (&g)[8], float (&dI)[2][16]) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 v = g[i];
+                *reinterpret_cast<float4*>(wl + stage64(4 * i + lane / 16, lane % 16)) = v;
+            }
+            wave_lds_fence();
 #pragma unroll
             for (int K = 0; K < 2; ++K)
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq) {
-                    const float4 v =
-                        *reinterpret_cast<const gfloat4*>(src + (32 * I + c) * 64 + 32 * K + 8 * qq + 4 * h);
-                    d[I][K][4 * qq] = v.x; d[I][K][4 * qq + 1] = v.y;
-                    d[I][K][4 * qq + 2] = v.z; d[I][K][4 * qq + 3] = v.w;
+                    const float4 v = *reinterpret_cast<const float4*>(wl + stage64(c, 8 * K + 2 * qq + h));
+                    dI[K][4 * qq] = v.x; dI[K][4 * qq + 1] = v.y;
+                    dI[K][4 * qq + 2] = v.z; dI[K][4 * qq + 3] = v.w;
                 }
+            wave_lds_fence();
+        };
+        half(g0, d[0]);
+        half(g1, d[1]);
         float m = 0.f;
 #pragma unroll
         for (int I = 0; I < 2; ++I)
@@ -840,14 +865,21 @@ k_mfma64(Addr a, int64_t batch, QTab q)
         // row 32 J + c, columns 32 I + 8 qq + 4 h .. +3 of Y
         gfloat* dst = a.dst(b);
 #pragma unroll
-        for (int I = 0; I < 2; ++I)
+        for (int J = 0; J < 2; ++J) {
 #pragma unroll
-            for (int J = 0; J < 2; ++J)
+            for (int I = 0; I < 2; ++I)
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq)
-                    *reinterpret_cast<gfloat4*>(dst + (32 * J + c) * 64 + 32 * I + 8 * qq + 4 * h) =
+                    *reinterpret_cast<float4*>(wl + stage64(c, 8 * I + 2 * qq + h)) =
                         make_float4(ldexpf(d[I][J][4 * qq], etot), ldexpf(d[I][J][4 * qq + 1], etot),
                                     ldexpf(d[I][J][4 * qq + 2], etot), ldexpf(d[I][J][4 * qq + 3], etot));
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                *reinterpret_cast<gfloat4*>(dst + 4 * (64 * (8 * J + i) + lane)) =
+                    *reinterpret_cast<const float4*>(wl + stage64(4 * i + lane / 16, lane % 16));
+            wave_lds_fence();
+        }
     }
 }
 
