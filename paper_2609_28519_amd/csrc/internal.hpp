@@ -203,6 +203,9 @@ int launch_rect256(const DeviceTables* t, const Job& j);
 // One array per workgroup in registers, both axes 32 .. 256 and one of 128 or 256 (kern_tile.hip).
 bool tile_shape(int rows, int cols);
 int launch_tile(const DeviceTables* t, const Job& j, bool persistent);
+// One axis of 8 or 16, the other of 128 or 256, a wavefront per tile of whole arrays (kern_band.hip).
+bool band_shape(int rows, int cols);
+int launch_band(const DeviceTables* t, const Job& j);
 int fp32_variant_count(int rows, int cols, int dir);
 int fp32_default_variant(int rows, int cols, int dir);
 int fp32_unshared_variant(int rows, int cols, int variant);

@@ -1879,7 +1879,8 @@ int launch_fused(const DeviceTables* t, const Job& j)
 //                     3 (short axis <= 64) k_rect256_db: one persistent workgroup per CU, two
 //                     tile buffers filled by LDS DMA while the other is transformed
 //   after these, where tile_shape holds: k_tile (kern_tile.hip), one array per workgroup, and then the
-//                     same with resident workgroups looping over the arrays
+//                     same with resident workgroups looping over the arrays; with a short axis of 8 or 16:
+//                     one variant, k_band (kern_band.hip)
 int fp32_tile_variant(int rows, int cols)
 {
     if (rows == 128 && cols == 128) return 6;
@@ -1892,7 +1893,7 @@ int fp32_variant_count(int rows, int cols, int)
 {
     if (rows == 64 && cols == 64) return 16;
     if (rows <= 64 && cols <= 64) return rows == cols ? 13 : 17;
-    return fp32_tile_variant(rows, cols) + (tile_shape(rows, cols) ? 2 : 0);
+    return fp32_tile_variant(rows, cols) + (tile_shape(rows, cols) ? 2 : band_shape(rows, cols) ? 1 : 0);
 }
 
 // Variant used until the tuner measures otherwise (fastest in measurements on MI355X
@@ -1928,11 +1929,9 @@ int fp32_default_variant(int rows, int cols, int dir)
         // against 252)
         return rows == 256 && cols <= 64 && dir == DCT2D_INVERSE ? 3 : tile;
     }
-    if ((rows == 256) != (cols == 256)) {
-        // the other axis is 8 or 16; measured on 512 MiB batches: the double-buffered kernel wherever it
-        // leads, but the round trip's arithmetic wants two workgroups per CU
-        return dir == DCT2D_ROUNDTRIP && cols == 256 ? 0 : 3;
-    }
+    // the other axis is 8 or 16: ahead of every other variant in each direction (narrowest 8 x 256 inverse, 240 us
+    // against 263 per 2^27 floats; widest 128 x 16 round trip, 300 against 654)
+    if (band_shape(rows, cols)) return fp32_tile_variant(rows, cols);
     return 0;
 }
 
@@ -1961,7 +1960,7 @@ int launch_fp32(const DeviceTables* t, const Job& j)
         return launch_two_pass(t, j);
     }
     const int tile = fp32_tile_variant(j.rows, j.cols);
-    if (j.variant >= tile) return launch_tile(t, j, j.variant > tile);
+    if (j.variant >= tile) return band_shape(j.rows, j.cols) ? launch_band(t, j) : launch_tile(t, j, j.variant > tile);
     if (j.rows == 128 && j.cols == 128) {
         if (j.variant == 0 || j.variant >= 3) return launch_split128(t, j, j.variant == 3 || j.variant == 4);
         if (j.variant == 1) return launch_fused(t, j);
