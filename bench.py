@@ -519,11 +519,12 @@ def kernel_name(n, d, tuned):
             return "k_split128<%d, %s>" % (di, "true" if v in (3, 4) else "false")
         return "k_fused<128, 128, %d>" % di if v == 1 else None
     if n == 256:
-        return None if v == 1 else "k_split256<%d>" % di
+        return None if v == 1 else "k_split256<%d>" % di if v < 5 else "k_tile<256, 256, %d>" % di
     return None
 
 
-KERNEL_SOURCES = ("kern_fp32.hip", "kern_rect256.hip", "fp32_common.hpp", "split256.hpp", "dct1d.hpp", "internal.hpp")
+KERNEL_SOURCES = ("kern_fp32.hip", "kern_rect256.hip", "kern_tile.hip", "kern_band.hip", "kern_line.hip", "kern_mix.hip",
+                  "fp32_common.hpp", "split256.hpp", "line_fft.hpp", "mix_fft.hpp", "dct1d.hpp", "internal.hpp")
 
 
 def source_digest():

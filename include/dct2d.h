@@ -33,17 +33,16 @@
  * Sizes accepted by the three basic calls and dct2d_transform_ex: rows and cols each
  * a power of two in [8, 1024] (squares and rectangles).  Axes up to 256 run the fused
  * kernels; a shape with an axis of 512 or 1024 runs two line passes, rows then columns,
- * the second in place on `out` (no workspace, no allocation): a 512- or 1024-point line is
- * split into its even/odd halves (Section 2.2) down to length-256 DCT-II/III and DCT-IV
- * transforms (the DCT-IV of a 512-point half through a 128-point complex FFT), each half
- * held by one wavefront and the halves combined through LDS.  Each pass reads and writes
- * the array once; the round trip is fused per line (forward, then inverse, in one pass).  Float32
+ * the second in place on `out` (no workspace, no allocation): two lines at a time go through
+ * one complex Fourier transform of their length, shared by length / 32 threads.  Each pass
+ * reads and writes the array once; the round trip is fused per line (forward, then inverse, in
+ * one pass).  Float32
  * path only (any other precision: DCT2D_ERR_PRECISION).  The variant, autotuner and
  * filter calls cover axes up to 256.  Any other length returns DCT2D_ERR_SIZE: like the
  * paper (Section 7.1) the basic API rejects non-power-of-two axes instead of
  * zero-padding, which would change the transform.  dct2d_image_transform and ragged
  * plans accept whole images with any axes in [8, 1024], including non-power-of-two
- * lengths (computed exactly from the dense Q_n of eq. 1).
+ * lengths (computed exactly, without padding).
  *
  * Alignment: `data`/`in`/`out` must be 16-byte aligned and strides multiples of 4
  * floats (DCT2D_ERR_ALIGN otherwise).
@@ -170,14 +169,15 @@ int dct2d_filter(const float* in, float* out, int64_t batch, int32_t rows, int32
  * Pointers, strides, alignment and in-place rules as dct2d_transform_ex.  Shapes with both
  * axes powers of two run the basic calls' kernels (DCT2D_AUTO; with an axis of 512 or 1024
  * the two line passes, which use no workspace).  Every other shape
- * is computed exactly from the dense Q_n of eq. 1 (Section 2.1; the paper's own library
- * rejects non-power-of-two axes, Section 7.1, rather than zero-padding them, which would
- * change the transform): one dense float32 product per axis (two for the round trip), with
- * the top even/odd level of Q_n's symmetry taken out where n is a multiple of 8.  The passes
- * go through a workspace of rows*cols floats per image (batch images, at most 65535 at a
- * time), taken from the stream-ordered allocator on `stream` and released on it; the dense
- * Q_n of each length is built once per device on first use (so the first call of a shape
- * synchronises the device) and kept until dct2d_finalize.
+ * is computed exactly (the paper's own library rejects non-power-of-two axes, Section 7.1,
+ * rather than zero-padding them, which would change the transform), one pass per axis, in place
+ * on the output and without a workspace: mixed-radix transforms of the axis's own length.  The
+ * exception are heights p, 2p and 3p with a large prime p (997, 998, 1011): one dense float32
+ * product with the Q_n of eq. 1 along the columns (two for the round trip), with the even/odd
+ * level of Q_n's symmetry taken out.  It goes through a workspace of rows*cols floats per image
+ * (batch images, at most 65535 at a time), taken from the stream-ordered allocator on `stream`
+ * and released on it; the dense Q_n of each such height is built once per device on first use
+ * (so the first call of it synchronises the device) and kept until dct2d_finalize.
  * Errors: DCT2D_ERR_SIZE (shape), DCT2D_ERR_NOMEM (workspace), as dct2d_transform_ex
  * otherwise. */
 int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, int32_t rows,
@@ -186,12 +186,13 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
 /* The same transform for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): allocates nothing and
  * never builds tables itself.  dct2d_init must have been called for the current device
- * (DCT2D_ERR_NOINIT otherwise).  The dense Q tables and the workspace live in a fixed
+ * (DCT2D_ERR_NOINIT otherwise).  Where the height takes the dense product, its Q table and
+ * the workspace live in a fixed
  * 64 MiB device array that the library holds on every device it runs on until the process
- * ends; the tables are rebuilt in it on `stream` by every call and the batch is processed in
- * chunks that fit (every accepted shape fits: the largest, 1024 x 1020, needs 12 MiB for one
- * image), so results equal dct2d_image_transform's.  Shapes whose axes are both powers of
- * two use none of the array (the basic calls' kernels, no tables, no workspace).  Calls on one device share that array: calls that
+ * ends; the table is rebuilt in it on `stream` by every call and the batch is processed in
+ * chunks that fit (every accepted shape fits: the largest, 1021 x 1024, needs 8 MiB for one
+ * image), so results equal dct2d_image_transform's.  Every other shape uses none of the
+ * array.  Calls on one device share that array: calls of such heights that
  * overlap in time on one device (different streams, or threads without ordering) race and
  * give wrong results.  Same arguments and errors as dct2d_image_transform, except that
  * DCT2D_ERR_SIZE also marks a shape needing more than the 64 MiB (none of the accepted
@@ -207,15 +208,16 @@ int dct2d_image_transform_noalloc(int dir, const float* in, float* out, int64_t 
  * with both axes powers of two <= 256 use the fast kernels of the basic calls, shapes
  * with both axes powers of two and one of 512 or 1024 (1024 x 1024, 64 x 1024) the two
  * float32 line passes of the basic calls, in place (whatever the plan's precision), and
- * any other shape (512 x 384) is computed with dense float32 Q_n tables (exact for
+ * any other shape (512 x 384) takes the passes of dct2d_image_transform (exact for
  * non-power-of-two axes; no zero-padding).
  *
  * dct2d_ragged_plan_create copies the (host) descriptor array, groups the items into
  * shape classes, uploads the per-class offset lists to the device, picks each class's
  * kernel configuration from the frozen per-size policy (the autotuner's table), and
- * records the whole batch as one HIP graph with one concurrent branch per class.  It
- * allocates device memory (once, here: offset lists, dense tables, the image
- * workspace).  `dir` is a DCT2D_* direction; `precision` DCT2D_FP32, DCT2D_AUTO or a
+ * records the whole batch as one HIP graph with one concurrent branch per class (small
+ * batches: as a chain of classes).  It
+ * allocates device memory (once, here: offset lists, and for heights that take the dense
+ * product its tables and a workspace).  `dir` is a DCT2D_* direction; `precision` DCT2D_FP32, DCT2D_AUTO or a
  * float32-accurate split path (DCT2D_SPLIT_BF16X6 / DCT2D_SPLIT_FP16X3, used for the
  * classes that have it).  Errors: DCT2D_ERR_SIZE (shape), DCT2D_ERR_ALIGN (offset not a
  * multiple of 4), DCT2D_ERR_ARG (overlap, empty, more than 65535 images of one shape).

@@ -217,7 +217,7 @@ def filter(inp, lam, out=None, stream=None):
 
 def image_transform(inp, out=None, direction="forward", stream=None, noalloc=False):
     """Batched transform of whole images of any shape with both axes in [8, 1024] (cols a multiple of
-    4), dense Q_n for axes the fast kernels do not cover (dct2d_image_transform); noalloc=True calls
+    4), computed exactly whatever the lengths (dct2d_image_transform); noalloc=True calls
     dct2d_image_transform_noalloc, which allocates nothing (dct2d_init must have run)."""
     import torch
     if out is None:

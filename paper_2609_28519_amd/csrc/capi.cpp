@@ -54,8 +54,8 @@ bool basic_size_ok(int rows, int cols)
 }
 
 // Power-of-two shapes with an axis of 512 or 1024 (the other 8 .. 1024): accepted by the
-// transform calls and computed by two passes over HBM whose long-axis lines are shared by two
-// or four wavefronts (kern_long.hip); no kernel variants, float32 path only.
+// transform calls and computed by two passes over HBM (kern_line.hip); no kernel variants, float32
+// path only.
 bool long_axis_size_ok(int rows, int cols)
 {
     return is_pow2(rows) && is_pow2(cols) && rows >= 8 && rows <= 1024 && cols >= 8 && cols <= 1024 &&

@@ -47,7 +47,7 @@ std::map<std::pair<int, int>, float*> g_q;
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 bool fast_shape(int r, int c) { return is_pow2(r) && is_pow2(c) && r >= 8 && r <= 256 && c >= 8 && c <= 256; }
-// power-of-two shapes with an axis of 512 or 1024: the two-pass long-axis kernels (no workspace)
+// power-of-two shapes with an axis of 512 or 1024: two line passes (no workspace)
 bool long_shape(int r, int c) { return is_pow2(r) && is_pow2(c) && r >= 8 && c >= 8 && r <= 1024 && c <= 1024 && (r > 256 || c > 256); }
 
 int validate(int dir, const float* in, const float* out, int64_t batch, int rows, int cols, int64_t in_stride,

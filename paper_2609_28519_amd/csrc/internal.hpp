@@ -181,7 +181,7 @@ int launch_fp32(const DeviceTables* t, const Job& j);
 // len <= 256 of `batch` arrays with lines_per_array lines each, one thread per line.
 int launch_short_line_pass(const DeviceTables* t, const Addr& a, int64_t batch, int len, int lines_per_array,
                            bool column_pass, int dir, hipStream_t s);
-// Power-of-two shapes with an axis of 512 or 1024, the other 8 .. 1024 (kern_long.hip): a row
+// Power-of-two shapes with an axis of 512 or 1024, the other 8 .. 1024 (kern_line.hip): a row
 // pass and a column pass, the second in place on the output.
 int launch_long(const DeviceTables* t, const Job& j);
 // A pass of direction `dir` along the rows or the columns of rows x cols arrays (cols a multiple of
