@@ -1922,9 +1922,10 @@ int fp32_default_variant(int rows, int cols, int dir)
     if (rows == 128 && cols == 128) return 4;
     if (tile_shape(rows, cols)) {
         const int tile = fp32_tile_variant(rows, cols);
-        // 256 x 256 forward: resident workgroups, whose next array's loads overlap the stores (265 us
-        // against 277 per 2^27 floats; inverse and round trip equal, every other shape slower)
-        if (rows == 256 && cols == 256) return dir == DCT2D_FORWARD ? tile + 1 : tile;
+        // 256 x 256: resident workgroups, whose next array's loads overlap the stores (forward / inverse /
+        // round trip 260 / 289 / 393 us against 265 / 293 / 400 per 2^27 floats); every other shape is slower
+        // with them (128 x 256 round trip 300 against 291, 256 x 128 325 / 315)
+        if (rows == 256 && cols == 256) return tile + 1;
         // the inverse of tall arrays runs as fast in k_rect256_db (256 x 64 260 against 262 us, 256 x 32 251
         // against 252)
         return rows == 256 && cols <= 64 && dir == DCT2D_INVERSE ? 3 : tile;

@@ -8,17 +8,18 @@
 // Bound: HBM where several workgroups share a CU (64 x 256 and below: 5.3 TB/s forward), else the sum of
 // the phases.  A 256 x 256 array takes the whole register file of a CU, so loads, arithmetic and stores
 // of an array overlap only across its own 16 wavefronts: the round trip issues 139 million wave
-// instructions (180 us) and 125 us of LDS beside 177 us of HBM, and takes 420.
+// instructions (180 us) and 125 us of LDS beside 177 us of HBM, and takes 393.
 //   * 64 values per thread and at most 128 registers: 16 wavefronts per CU, twice those of k_split256
 //     and four times those of k_rect256_db.  Nothing may spill for that: at 300 bytes of scratch per
-//     thread the 256 x 256 round trip took 700 us.
+//     thread the 256 x 256 round trip took 700 us, at 84 (the row pass's offsets held across the columns)
+//     403, and that of 128 x 256 346 instead of 295.
 //   * the LDS tile holds half an array: a transposition is two rounds (transpose below).
 // 2^27 floats, out of place, us, the best kernel before -> now (forward / inverse / round trip):
-//   256 x 256  292 -> 265, 303 -> 288, 432 -> 420    128 x 256  497 -> 210, 413 -> 208, 529 -> 346
-//   256 x 128  487 -> 230, 472 -> 227, 614 -> 364    64 x 256   284 -> 203, 279 -> 201, 462 -> 297
-//   256 x 64   284 -> 251, 260 -> 262, 473 -> 380    32 x 256   281 -> 195, 271 -> 197, 457 -> 254
-//   256 x 32   288 -> 218, 251 -> 252, 453 -> 316    64 x 128   424 -> 203, 425 -> 202, 478 -> 263
-//   128 x 64   426 -> 220, 424 -> 258, 490 -> 331    32 x 128   454 -> 208, 447 -> 202, 561 -> 263
+//   256 x 256  292 -> 265, 303 -> 288, 432 -> 393    128 x 256  497 -> 210, 413 -> 208, 529 -> 295
+//   256 x 128  487 -> 230, 472 -> 222, 614 -> 315    64 x 256   284 -> 203, 279 -> 201, 462 -> 308
+//   256 x 64   284 -> 251, 260 -> 262, 473 -> 370    32 x 256   281 -> 195, 271 -> 197, 457 -> 257
+//   256 x 32   288 -> 218, 251 -> 252, 453 -> 326    64 x 128   424 -> 203, 425 -> 202, 478 -> 271
+//   128 x 64   426 -> 220, 424 -> 258, 490 -> 323    32 x 128   454 -> 208, 447 -> 202, 561 -> 275
 //   128 x 32   434 -> 208, 426 -> 261, 591 -> 294
 // (Tall arrays trail wide ones: eight threads share a column pair of 256 rows, so a wavefront covers 16
 // columns, 64 bytes of a row.)
@@ -47,7 +48,7 @@ struct TileCfg {
     static constexpr int LDS = mx(mx(WAVES * XW, H * PT), H / HALVES * PB);
     // wavefronts per SIMD that the registers are held to: a CU takes 1024 threads of the larger
     // shapes (two workgroups, or one), 768 of the smaller
-    static constexpr int OCC = NT >= 512 ? 4 : 3;
+    static constexpr int OCC = NT >= 256 ? 4 : 3;
     static constexpr int TABW = 2 * LineCfg<W>::TAB, TABH = H == W ? 0 : 2 * LineCfg<H>::TAB;
 };
 
@@ -247,6 +248,10 @@ k_tile(Addr a, int64_t batch, float s0w, float s0h, const float2* __restrict__ t
             settle(lo, hi);
             line::from_slots(v, c0, lo, hi);
             line::fft_inverse<H, typename C::CP>(v, X, ct, cps, th, wave_sync);
+            // formed anew: the first row pass's offsets are not held across the columns (84 bytes of scratch)
+            asm volatile("" : "+v"(lane));
+            const int rps = lane / LW::TPL, rt = lane % LW::TPL, row = 2 * (wave * C::RS + rps);
+            const bool r0 = rt == 0;
             // ---- back to rows, by halves of the columns
             auto put = [&](int h) {
 #pragma unroll
