@@ -291,7 +291,7 @@ int band_run(const DeviceTables* t, const Job& j)
     constexpr int N = H > W ? H : W, PER = 4096 / (H * W) * kBandWaves;
     const int64_t grid = (j.batch + PER - 1) / PER;
     if (grid > 0x7fffffff) return DCT2D_ERR_ARG;
-    const float s0 = (float)(1.0 / __builtin_sqrt((double)N));
+    const float s0 = line_s0(N);
     if constexpr (W > H)
         k_band_wide<H, W, DIR><<<(unsigned)grid, 64 * kBandWaves, 0, j.stream>>>(j.addr(), j.batch, s0, line_tab_for(t, N), tw_for(t, H));
     else

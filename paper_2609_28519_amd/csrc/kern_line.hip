@@ -228,8 +228,7 @@ int run(const DeviceTables* t, const Addr& a, int64_t batch, int lines, int es, 
     const int64_t tiles = (lines / 2 + S::SLOTS - 1) / S::SLOTS, total = batch * tiles;
     if (total > 0x7fffffff) return DCT2D_ERR_ARG;
     k_line<N, DIR, COLS, PAIRS><<<(unsigned)((total + S::TILES - 1) / S::TILES), S::NT, 0, s>>>(
-        a, (uint32_t)total, (uint32_t)tiles, (uint32_t)(lines / 2), es, ls, (float)(1.0 / __builtin_sqrt((double)N)),
-        line_tab_for(t, N));
+        a, (uint32_t)total, (uint32_t)tiles, (uint32_t)(lines / 2), es, ls, line_s0(N), line_tab_for(t, N));
     return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
 }
 

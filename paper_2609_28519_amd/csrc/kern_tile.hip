@@ -315,8 +315,7 @@ int tile_run(const DeviceTables* t, const Job& j, bool persistent)
     int64_t grid = j.batch;
     if (persistent && grid > (int64_t)t->num_cu * (1024 / C::NT)) grid = (int64_t)t->num_cu * (1024 / C::NT);
     if (grid > 0x7fffffff) grid = 0x7fffffff;
-    k_tile<H, W, DIR><<<(unsigned)grid, C::NT, 0, j.stream>>>(j.addr(), j.batch, (float)(1.0 / __builtin_sqrt((double)W)),
-                                                              (float)(1.0 / __builtin_sqrt((double)H)),
+    k_tile<H, W, DIR><<<(unsigned)grid, C::NT, 0, j.stream>>>(j.addr(), j.batch, line_s0(W), line_s0(H),
                                                               line_tab_for(t, W), line_tab_for(t, H));
     return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
 }

@@ -7,6 +7,11 @@
 //   X_a[k] = Re(c U),  X_a[N-k] = -Im(c U),  X_b[k] = Im(c D),  X_b[N-k] = Re(c D).
 // The inverse is the transposed graph with the same constants (Section 2.2, Prop. 2).
 //
+// The table holds c_k / S with a power of two S (line_scale), and the last butterflies of the DFT, in
+// either direction, multiply by S.  Forward, U and D then do not leave the range of float32 where Z
+// does not (a single value of 3e38 came out as infinities); inverse, the factors that multiply first are
+// near 1/2, so that subnormal coefficients keep their bits (256 x 256 inverse of 1e-40: 2.4e-4 without).
+//
 // The DFT is N = R1 * R2 * 16 (R2 = 1 leaves out the middle stage), n = r1 + T1 m, T1 = N / R1,
 // r1 = r2 + 16 m2, k = j3 + T3 q, T3 = N / 16, j3 = p + R1 p2:
 //   stage 1  radix R1 over m, times W_N^{r1 p}
@@ -25,7 +30,7 @@ namespace dct {
 
 // Stages, and the table of a length (complex entries):
 //   [0, N)           W_N^{r1 p} at p * T1 + r1           (copied to LDS by each workgroup)
-//   [N, N + N / 2)   c_k of slot q, thread t, at q * TPL + t (likewise; slots below)
+//   [N, N + N / 2)   c_k / S of slot q, thread t, at q * TPL + t (likewise; slots below)
 //   MID .. + T1      W_{T1}^{r2 p2} at 16 p2 + r2
 struct LinePlan {
     int n, r1, r2;
@@ -35,6 +40,11 @@ constexpr LinePlan line_plan(int n)
     return n == 1024 ? LinePlan{n, 16, 4} : n == 512 ? LinePlan{n, 16, 2} : LinePlan{n, n / 16, 1};
 }
 constexpr int line_table_size(int n) { return n + n / 2 + n / line_plan(n).r1; }
+// S: c_k / S lies between 0.35 and 0.5, so that neither the inverse's first products nor the sum of the
+// two that a single coefficient has overflow, and the last layer's roundings stay below c's own.
+constexpr float line_scale(int n) { return n <= 64 ? 0.25f : n <= 256 ? 0.125f : 0.0625f; }
+// The factor of the unpaired coefficients 0 and N / 2.
+inline float line_s0(int n) { return (float)(1.0 / __builtin_sqrt((double)n)) / line_scale(n); }
 
 template <int N>
 struct LineCfg {
@@ -43,6 +53,8 @@ struct LineCfg {
     static constexpr int T1 = N / R1, T3 = N / 16, TPL = N / 32; // TPL: threads per line pair
     static constexpr int NB = 32 / R1;                           // stage-1 butterflies per thread
     static constexpr int TAB = N + N / 2, MID = TAB;             // entries kept in LDS
+    static constexpr int SH = line_scale(N) == 0.25f ? 2 : line_scale(N) == 0.125f ? 3 : 4; // S = 2^-SH
+    static_assert(line_scale(N) * (1 << SH) == 1.f, "S is a power of two");
 };
 
 namespace line {
@@ -59,39 +71,52 @@ __device__ __forceinline__ cf turn(cf a, float c, float s)
     return INV ? cf{a.x * c - a.y * s, a.y * c + a.x * s} : cf{a.x * c + a.y * s, a.y * c - a.x * s};
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft2(cf& a, cf& b)
+// (a + b, a - b) / 2^SH, the halvings folded into the additions
+template <int SH>
+__device__ __forceinline__ void butterfly(cf& a, cf& b)
 {
-    const cf t = a;
-    a = cadd(t, b);
-    b = csub(t, b);
+    if constexpr (SH == 0) {
+        const cf t = a;
+        a = cadd(t, b);
+        b = csub(t, b);
+    } else {
+        constexpr float S = 1.f / (1 << SH);
+        const cf t = {S * a.x, S * a.y};
+        a = {__builtin_fmaf(S, b.x, t.x), __builtin_fmaf(S, b.y, t.y)};
+        b = {__builtin_fmaf(-S, b.x, t.x), __builtin_fmaf(-S, b.y, t.y)};
+    }
 }
 
-template <bool INV>
+// The DFTs of R values, times 2^-SH.
+template <bool INV, int SH = 0>
 __device__ __forceinline__ void dft4(cf& a, cf& b, cf& c, cf& d)
 {
-    const cf t0 = cadd(a, c), t1 = csub(a, c), t2 = cadd(b, d), t3 = rot<INV>(csub(b, d));
-    a = cadd(t0, t2);
-    b = cadd(t1, t3);
-    c = csub(t0, t2);
-    d = csub(t1, t3);
+    cf t0 = cadd(a, c), t1 = csub(a, c), t2 = cadd(b, d), t3 = rot<INV>(csub(b, d));
+    butterfly<SH>(t0, t2);
+    butterfly<SH>(t1, t3);
+    a = t0;
+    b = t1;
+    c = t2;
+    d = t3;
 }
 
-template <bool INV>
+template <bool INV, int SH = 0>
 __device__ __forceinline__ void dft8(cf* v)
 {
     constexpr float h = 0.70710678118654752f;
     dft4<INV>(v[0], v[2], v[4], v[6]);
     dft4<INV>(v[1], v[3], v[5], v[7]);
-    const cf o1 = turn<INV>(v[3], h, h), o2 = rot<INV>(v[5]), o3 = turn<INV>(v[7], -h, h);
-    const cf e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6], o0 = v[1];
-    v[0] = cadd(e0, o0); v[4] = csub(e0, o0);
-    v[1] = cadd(e1, o1); v[5] = csub(e1, o1);
-    v[2] = cadd(e2, o2); v[6] = csub(e2, o2);
-    v[3] = cadd(e3, o3); v[7] = csub(e3, o3);
+    cf o0 = v[1], o1 = turn<INV>(v[3], h, h), o2 = rot<INV>(v[5]), o3 = turn<INV>(v[7], -h, h);
+    cf e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
+    butterfly<SH>(e0, o0);
+    butterfly<SH>(e1, o1);
+    butterfly<SH>(e2, o2);
+    butterfly<SH>(e3, o3);
+    v[0] = e0; v[1] = e1; v[2] = e2; v[3] = e3;
+    v[4] = o0; v[5] = o1; v[6] = o2; v[7] = o3;
 }
 
-template <bool INV>
+template <bool INV, int SH = 0>
 __device__ __forceinline__ void dft16(cf* v)
 {
     constexpr float h = 0.70710678118654752f, c1 = 0.92387953251128674f, s1 = 0.38268343236508977f;
@@ -108,7 +133,7 @@ __device__ __forceinline__ void dft16(cf* v)
     v[14] = turn<INV>(v[14], -h, h);
     v[15] = turn<INV>(v[15], -c1, -s1);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) dft4<INV>(v[4 * p], v[4 * p + 1], v[4 * p + 2], v[4 * p + 3]);
+    for (int p = 0; p < 4; ++p) dft4<INV, SH>(v[4 * p], v[4 * p + 1], v[4 * p + 2], v[4 * p + 3]);
     // output p + 4 q sits at v[4 p + q]: transpose
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -120,13 +145,13 @@ __device__ __forceinline__ void dft16(cf* v)
         }
 }
 
-template <int R, bool INV>
+template <int R, bool INV, int SH = 0>
 __device__ __forceinline__ void dft(cf* v)
 {
-    if constexpr (R == 2) dft2<INV>(v[0], v[1]);
-    else if constexpr (R == 4) dft4<INV>(v[0], v[1], v[2], v[3]);
-    else if constexpr (R == 8) dft8<INV>(v);
-    else if constexpr (R == 16) dft16<INV>(v);
+    if constexpr (R == 2) butterfly<SH>(v[0], v[1]);
+    else if constexpr (R == 4) dft4<INV, SH>(v[0], v[1], v[2], v[3]);
+    else if constexpr (R == 8) dft8<INV, SH>(v);
+    else if constexpr (R == 16) dft16<INV, SH>(v);
 }
 
 // Times a table twiddle (conjugated for the inverse).
@@ -230,7 +255,7 @@ struct Twiddles {
     __device__ __forceinline__ float2 slot(int q, int t) const { return tab[N + q * C::TPL + t]; }
 };
 
-// Forward: v[i * R1 + m] = z[r1_of(i) + T1 m]  ->  v[16 i + q] = Z[j3_of(i) + T3 q].
+// Forward: v[i * R1 + m] = z[r1_of(i) + T1 m]  ->  v[16 i + q] = S Z[j3_of(i) + T3 q].
 template <int N, class P, class SYNC>
 __device__ __forceinline__ void fft_forward(cf (&v)[32], float* lds, int t, int ps, const Twiddles<N>& w, SYNC sync)
 {
@@ -265,11 +290,11 @@ __device__ __forceinline__ void fft_forward(cf (&v)[32], float* lds, int t, int 
             lds, v, [&](int i) { return P::ex2(i % R1, r1_of<N>(t, i / R1), ps); },
             [&](int i) { return P::ex2(j3_of<N>(t, i / 16), i % 16, ps); }, sync);
     }
-    dft16<false>(v);
-    dft16<false>(v + 16);
+    dft16<false, C::SH>(v);
+    dft16<false, C::SH>(v + 16);
 }
 
-// The transposed graph: v[16 i + q] = Z[j3_of(i) + T3 q]  ->  v[i * R1 + m] = z[r1_of(i) + T1 m].
+// The transposed graph: v[16 i + q] = Z[j3_of(i) + T3 q]  ->  v[i * R1 + m] = S z[r1_of(i) + T1 m].
 template <int N, class P, class SYNC>
 __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int ps, const Twiddles<N>& w, SYNC sync)
 {
@@ -304,7 +329,7 @@ __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int 
 #pragma unroll
     for (int i = 0; i < C::NB; ++i) {
         w.template stage1<true>(v + i * R1, r1_of<N>(t, i));
-        dft<R1, true>(v + i * R1);
+        dft<R1, true, C::SH>(v + i * R1);
     }
 }
 

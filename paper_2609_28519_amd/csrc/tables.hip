@@ -122,7 +122,7 @@ __global__ void k_line_table(float2* out, int n, int r1)
     } else if (i < n + n / 2) { // slot q of thread t: k = t + T3 q; thread 0, q >= 8: k = T3 / 2 + T3 q
         const int q = (i - n) / TPL, t = (i - n) % TPL;
         ang = 0.5 * (T3 * q + (q >= 8 && t == 0 ? T3 / 2 : t)) / n;
-        a = 0.5 * sqrt(2.0 / n);
+        a = 0.5 * sqrt(2.0 / n) / line_scale(n);
     } else if (i < n + n / 2 + T1) {
         const int j = i - n - n / 2;
         ang = 2.0 * ((j % 16) * (j / 16) % T1) / T1;
