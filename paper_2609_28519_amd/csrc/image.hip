@@ -124,7 +124,7 @@ int dct::launch_image(const DeviceTables* t, const Job& j, float* ws, const floa
     const Addr in = j.addr();
     const Addr out{j.out, j.out, j.out_stride, j.out_stride, j.out_idx, j.out_idx, j.out_slot, j.out_slot};
     auto line = [&](const Addr& a, bool column_pass) {
-        return launch_line_axis(t, a, j.batch, j.rows, j.cols, column_pass, j.dir, j.stream);
+        return launch_line_axis(t, a, j.batch, j.rows, j.cols, column_pass, j.dir, true, j.stream);
     };
     if (line_axis(j.rows)) {
         const int rc = line(in, false);

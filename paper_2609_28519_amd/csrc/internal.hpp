@@ -178,9 +178,10 @@ int launch_dense_columns(const Addr& a, int64_t count, int rows, int cols, bool 
 
 int launch_fp32(const DeviceTables* t, const Job& j);
 // One pass of direction `dir` along the rows (or, column_pass, the columns) of length
-// len <= 256 of `batch` arrays with lines_per_array lines each, one thread per line.
+// len <= 256 of `batch` arrays with lines_per_array lines each, one thread per line.  norm (len <= 128): as
+// launch_line_axis.
 int launch_short_line_pass(const DeviceTables* t, const Addr& a, int64_t batch, int len, int lines_per_array,
-                           bool column_pass, int dir, hipStream_t s);
+                           bool column_pass, int dir, bool norm, hipStream_t s);
 // Power-of-two shapes with an axis of 512 or 1024, the other 8 .. 1024 (kern_line.hip): a row
 // pass and a column pass, the second in place on the output.
 int launch_long(const DeviceTables* t, const Job& j);
@@ -190,10 +191,12 @@ bool mix_smooth(int n);
 int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass, int dir,
                     hipStream_t s);
 // The same along an axis of any length that transforms its lines in place: powers of two and
-// the lengths that mix_smooth admits (line_axis).
+// the lengths that mix_smooth admits (line_axis).  norm: whole images, whose amplitudes may come within a
+// small factor of what the result can represent (as in a product with Q_n, which has no larger
+// intermediate values); otherwise a power-of-two axis sums its values before it scales them.
 bool line_axis(int n);
 int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass,
-                     int dir, hipStream_t s);
+                     int dir, bool norm, hipStream_t s);
 // Whole images (both axes in [8, 1024], not both powers of two, cols a multiple of 4, which makes it a
 // line_axis).  Rows outside line_axis take a dense product: it needs Q_rows and a workspace of
 // rows * cols floats per image.

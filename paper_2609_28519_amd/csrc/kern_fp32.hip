@@ -1440,7 +1440,19 @@ k_split256(Addr a, int64_t batch, const float2* __restrict__ tw_in, int stagger)
 }
 
 // Row pass over HBM: one thread per row of length L (rows of `rows` per array).
-template <int L, int DIR>
+// Powers of two that keep the sums of a line of whole images in range (NORM): the line times 2^-norm_shift
+// (at least 1 / sqrt L) before its transform, and the result times 2^norm_shift.
+constexpr int norm_shift(int L) { return L >= 64 ? 3 : L >= 16 ? 2 : 1; }
+template <int L, bool NORM>
+__device__ __forceinline__ void norm_scale(float (&v)[L], float f)
+{
+    if constexpr (NORM) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) v[i] *= f;
+    }
+}
+
+template <int L, int DIR, bool NORM>
 __global__ void __launch_bounds__(64)
 k_rows(Addr a, int64_t batch, int32_t rows, const float2* __restrict__ tw_in)
 {
@@ -1457,7 +1469,9 @@ k_rows(Addr a, int64_t batch, int32_t rows, const float2* __restrict__ tw_in)
         const float4 q = *reinterpret_cast<const gfloat4*>(src + 4 * j);
         v[4 * j] = q.x; v[4 * j + 1] = q.y; v[4 * j + 2] = q.z; v[4 * j + 3] = q.w;
     }
+    norm_scale<L, NORM>(v, 1.f / (1 << norm_shift(L)));
     apply1d<L, DIR>(v, tw);
+    norm_scale<L, NORM>(v, (float)(1 << norm_shift(L)));
 #pragma unroll
     for (int j = 0; j < L / 4; ++j)
         *reinterpret_cast<gfloat4*>(dst + 4 * j) = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
@@ -1465,7 +1479,7 @@ k_rows(Addr a, int64_t batch, int32_t rows, const float2* __restrict__ tw_in)
 
 // Column pass over HBM: one thread per column of length L; consecutive lanes take
 // consecutive columns, so every load/store instruction is contiguous across the wave.
-template <int L, int DIR>
+template <int L, int DIR, bool NORM>
 __global__ void __launch_bounds__(64)
 k_cols(Addr a, int64_t batch, int32_t cols, const float2* __restrict__ tw_in)
 {
@@ -1479,10 +1493,12 @@ k_cols(Addr a, int64_t batch, int32_t cols, const float2* __restrict__ tw_in)
     float v[L];
 #pragma unroll
     for (int r = 0; r < L; ++r) v[r] = src[(int64_t)r * cols];
+    norm_scale<L, NORM>(v, 1.f / (1 << norm_shift(L)));
     if constexpr (DIR == DIR_FILTER)
         filter1d<L>(v, a.lam_for(b) + c, cols, tw);
     else
         apply1d<L, DIR>(v, tw);
+    norm_scale<L, NORM>(v, (float)(1 << norm_shift(L)));
 #pragma unroll
     for (int r = 0; r < L; ++r) dst[(int64_t)r * cols] = v[r];
 }
@@ -1735,68 +1751,74 @@ int launch_split256(const DeviceTables* t, const Job& j)
     }
 }
 
-template <int L, int DIR>
+template <int L, int DIR, bool NORM>
 void launch_rows(const DeviceTables* t, const Addr& a, int64_t batch, int rows, hipStream_t s)
 {
     const int64_t n = batch * rows;
-    k_rows<L, DIR><<<(unsigned)((n + 63) / 64), 64, 0, s>>>(a, batch, rows, tw_for(t, L));
+    k_rows<L, DIR, NORM><<<(unsigned)((n + 63) / 64), 64, 0, s>>>(a, batch, rows, tw_for(t, L));
 }
 
-template <int L, int DIR>
+template <int L, int DIR, bool NORM>
 void launch_cols(const DeviceTables* t, const Addr& a, int64_t batch, int cols, hipStream_t s)
 {
     const int64_t n = batch * cols;
-    k_cols<L, DIR><<<(unsigned)((n + 63) / 64), 64, 0, s>>>(a, batch, cols, tw_for(t, L));
+    k_cols<L, DIR, NORM><<<(unsigned)((n + 63) / 64), 64, 0, s>>>(a, batch, cols, tw_for(t, L));
 }
 
 // Row pass with length `len` (runtime) -> template dispatch.
-template <int DIR>
+template <int DIR, bool NORM = false>
 int rows_any(const DeviceTables* t, int len, const Addr& a, int64_t batch, int rows, hipStream_t s)
 {
     switch (len) {
-    case 8: launch_rows<8, DIR>(t, a, batch, rows, s); break;
-    case 16: launch_rows<16, DIR>(t, a, batch, rows, s); break;
-    case 32: launch_rows<32, DIR>(t, a, batch, rows, s); break;
-    case 64: launch_rows<64, DIR>(t, a, batch, rows, s); break;
-    case 128: launch_rows<128, DIR>(t, a, batch, rows, s); break;
-    case 256: launch_rows<256, DIR>(t, a, batch, rows, s); break;
+    case 8: launch_rows<8, DIR, NORM>(t, a, batch, rows, s); break;
+    case 16: launch_rows<16, DIR, NORM>(t, a, batch, rows, s); break;
+    case 32: launch_rows<32, DIR, NORM>(t, a, batch, rows, s); break;
+    case 64: launch_rows<64, DIR, NORM>(t, a, batch, rows, s); break;
+    case 128: launch_rows<128, DIR, NORM>(t, a, batch, rows, s); break;
+    case 256:
+        if constexpr (NORM) return DCT2D_ERR_SIZE;
+        else launch_rows<256, DIR, false>(t, a, batch, rows, s);
+        break;
+    default: return DCT2D_ERR_SIZE;
+    }
+    return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
+}
+
+template <int DIR, bool NORM = false>
+int cols_any(const DeviceTables* t, int len, const Addr& a, int64_t batch, int cols, hipStream_t s)
+{
+    switch (len) {
+    case 8: launch_cols<8, DIR, NORM>(t, a, batch, cols, s); break;
+    case 16: launch_cols<16, DIR, NORM>(t, a, batch, cols, s); break;
+    case 32: launch_cols<32, DIR, NORM>(t, a, batch, cols, s); break;
+    case 64: launch_cols<64, DIR, NORM>(t, a, batch, cols, s); break;
+    case 128: launch_cols<128, DIR, NORM>(t, a, batch, cols, s); break;
+    case 256:
+        if constexpr (NORM) return DCT2D_ERR_SIZE;
+        else launch_cols<256, DIR, false>(t, a, batch, cols, s);
+        break;
     default: return DCT2D_ERR_SIZE;
     }
     return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
 }
 
 template <int DIR>
-int cols_any(const DeviceTables* t, int len, const Addr& a, int64_t batch, int cols, hipStream_t s)
+int any_axis(const DeviceTables* t, int len, const Addr& a, int64_t batch, int lines, bool column_pass, bool norm, hipStream_t s)
 {
-    switch (len) {
-    case 8: launch_cols<8, DIR>(t, a, batch, cols, s); break;
-    case 16: launch_cols<16, DIR>(t, a, batch, cols, s); break;
-    case 32: launch_cols<32, DIR>(t, a, batch, cols, s); break;
-    case 64: launch_cols<64, DIR>(t, a, batch, cols, s); break;
-    case 128: launch_cols<128, DIR>(t, a, batch, cols, s); break;
-    case 256: launch_cols<256, DIR>(t, a, batch, cols, s); break;
-    default: return DCT2D_ERR_SIZE;
-    }
-    return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
+    if (norm) return column_pass ? cols_any<DIR, true>(t, len, a, batch, lines, s) : rows_any<DIR, true>(t, len, a, batch, lines, s);
+    return column_pass ? cols_any<DIR>(t, len, a, batch, lines, s) : rows_any<DIR>(t, len, a, batch, lines, s);
 }
 
 } // namespace
 
 int launch_short_line_pass(const DeviceTables* t, const Addr& a, int64_t batch, int len, int lines_per_array,
-                           bool column_pass, int dir, hipStream_t s)
+                           bool column_pass, int dir, bool norm, hipStream_t s)
 {
     switch (dir) {
-    case DCT2D_FORWARD:
-        return column_pass ? cols_any<DCT2D_FORWARD>(t, len, a, batch, lines_per_array, s)
-                           : rows_any<DCT2D_FORWARD>(t, len, a, batch, lines_per_array, s);
-    case DCT2D_INVERSE:
-        return column_pass ? cols_any<DCT2D_INVERSE>(t, len, a, batch, lines_per_array, s)
-                           : rows_any<DCT2D_INVERSE>(t, len, a, batch, lines_per_array, s);
-    case DCT2D_ROUNDTRIP:
-        return column_pass ? cols_any<DCT2D_ROUNDTRIP>(t, len, a, batch, lines_per_array, s)
-                           : rows_any<DCT2D_ROUNDTRIP>(t, len, a, batch, lines_per_array, s);
-    default:
-        return DCT2D_ERR_ARG;
+    case DCT2D_FORWARD: return any_axis<DCT2D_FORWARD>(t, len, a, batch, lines_per_array, column_pass, norm, s);
+    case DCT2D_INVERSE: return any_axis<DCT2D_INVERSE>(t, len, a, batch, lines_per_array, column_pass, norm, s);
+    case DCT2D_ROUNDTRIP: return any_axis<DCT2D_ROUNDTRIP>(t, len, a, batch, lines_per_array, column_pass, norm, s);
+    default: return DCT2D_ERR_ARG;
     }
 }
 

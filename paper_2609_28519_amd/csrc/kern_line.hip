@@ -48,7 +48,7 @@ __device__ __forceinline__ void lds_sync()
     else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int N, int DIR, bool COLS, int PAIRS>
+template <int N, int DIR, bool COLS, int PAIRS, bool NORM>
 __global__ void __launch_bounds__((Shape<N, COLS, PAIRS>::NT), COLS && PAIRS == 16 && N >= 512 ? 4 : 3)
 k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32_t ls, float s0,
        const float2* __restrict__ tab_in)
@@ -113,6 +113,8 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
             *reinterpret_cast<gfloat*>(dst + c * 4 + (o + (uint32_t)ls * 4u)) = xb;
         }
     };
+    using F = line::Norm<N, NORM>;
+    auto scaled = [](float2 c, float f) { return f == 1.f ? c : make_float2(c.x * f, c.y * f); };
     auto lo_lane = [&](int q) { return line::lo_lane<N>(t, q); };
     auto hi_lane = [&](int q) { return line::hi_lane<N>(t, q); };
     if constexpr (DIR == DCT2D_INVERSE) {
@@ -129,7 +131,7 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
         for (int q = 0; q < 16; ++q) {
             cf l, h;
             line::slot_inverse<N>({lo[q].x, hi[q].x}, {lo[q].y, hi[q].y}, q == 0 && t0,
-                                  tw.slot(q, t), s0, l, h);
+                                  scaled(tw.slot(q, t), F::inv_c), s0 * F::inv_c, l, h);
             lo[q] = l;
             hi[q] = h;
         }
@@ -159,16 +161,16 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
 #pragma unroll
         for (int i = 0; i < COPIES; ++i) *(reinterpret_cast<float4*>(lds_all) + tc_at(i)) = tc[i];
         lds_sync<false>();
-        line::fft_forward<N, P>(v, lds, t, ps, tw, sync);
+        line::fft_forward<N, P, NORM>(v, lds, t, ps, tw, sync);
         cf lo[16], hi[16];
         line::to_slots(v, t0, lo, hi);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             cf xa, xb;
             const float2 c = tw.slot(q, t);
-            line::slot_forward<N>(lo[q], hi[q], q == 0 && t0, c, s0, xa, xb);
+            line::slot_forward<N>(lo[q], hi[q], q == 0 && t0, scaled(c, F::fwd_c), s0 * F::fwd_c, xa, xb);
             if constexpr (DIR == DCT2D_ROUNDTRIP) {
-                line::slot_inverse<N>(xa, xb, q == 0 && t0, c, s0, lo[q], hi[q]);
+                line::slot_inverse<N>(xa, xb, q == 0 && t0, scaled(c, F::inv_c), s0 * F::inv_c, lo[q], hi[q]);
             } else if constexpr (COLS) {
                 store_k(lane(lo_lane(q)), line::lo_const<N>(q), xa.x, xb.x);
                 store_k(lane(hi_lane(q)), line::hi_const<N>(q), xa.y, xb.y);
@@ -201,7 +203,7 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
         if constexpr (DIR == DCT2D_FORWARD) return;
         line::from_slots(v, t0, lo, hi);
     }
-    line::fft_inverse<N, P>(v, lds, t, ps, tw, sync);
+    line::fft_inverse<N, P, NORM>(v, lds, t, ps, tw, sync);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int mi = line::mirror<N>(i);
@@ -221,43 +223,50 @@ k_line(Addr a, uint32_t total, uint32_t tiles, uint32_t pairs, int32_t es, int32
     }
 }
 
-template <int N, int DIR, bool COLS, int PAIRS>
+template <int N, int DIR, bool COLS, int PAIRS, bool NORM>
 int run(const DeviceTables* t, const Addr& a, int64_t batch, int lines, int es, int ls, hipStream_t s)
 {
     using S = Shape<N, COLS, PAIRS>;
     const int64_t tiles = (lines / 2 + S::SLOTS - 1) / S::SLOTS, total = batch * tiles;
     if (total > 0x7fffffff) return DCT2D_ERR_ARG;
-    k_line<N, DIR, COLS, PAIRS><<<(unsigned)((total + S::TILES - 1) / S::TILES), S::NT, 0, s>>>(
+    k_line<N, DIR, COLS, PAIRS, NORM><<<(unsigned)((total + S::TILES - 1) / S::TILES), S::NT, 0, s>>>(
         a, (uint32_t)total, (uint32_t)tiles, (uint32_t)(lines / 2), es, ls, line_s0(N), line_tab_for(t, N));
     return hipGetLastError() == hipSuccess ? DCT2D_OK : DCT2D_ERR_HIP;
 }
 
-template <int N, bool COLS, int PAIRS>
+template <int N, bool COLS, int PAIRS, bool NORM>
 int run_dir(const DeviceTables* t, const Addr& a, int64_t batch, int lines, int es, int ls, int dir, hipStream_t s)
 {
     switch (dir) {
-    case DCT2D_FORWARD: return run<N, DCT2D_FORWARD, COLS, PAIRS>(t, a, batch, lines, es, ls, s);
-    case DCT2D_INVERSE: return run<N, DCT2D_INVERSE, COLS, PAIRS>(t, a, batch, lines, es, ls, s);
-    default: return run<N, DCT2D_ROUNDTRIP, COLS, PAIRS>(t, a, batch, lines, es, ls, s);
+    case DCT2D_FORWARD: return run<N, DCT2D_FORWARD, COLS, PAIRS, NORM>(t, a, batch, lines, es, ls, s);
+    case DCT2D_INVERSE: return run<N, DCT2D_INVERSE, COLS, PAIRS, NORM>(t, a, batch, lines, es, ls, s);
+    default: return run<N, DCT2D_ROUNDTRIP, COLS, PAIRS, NORM>(t, a, batch, lines, es, ls, s);
     }
 }
 
-// Column tiles.  32 columns (16 pairs) keep 128-byte accesses but take 512 threads at N = 512 and
-// 1024, whose 128 registers the round trip overflows (and at 1024 the forward too); 16 columns run
-// with 168 registers (512 x 512: forward 422 / 439, round trip 515 / 480 us for 32 / 16 columns; 1024 x
-// 1024: forward 436 / 435, round trip 593 / 524).  An array of 8 columns is one tile.
-template <int N>
+// Column tiles.  32 columns (16 pairs) keep 128-byte accesses but take 512 threads at N = 1024, whose
+// 128 registers the forward and the round trip overflow; 16 columns run with 168 registers (512 x 512: forward
+// 422 / 439, round trip 515 / 480 us for 32 / 16 columns; 1024 x 1024: forward 436 / 435, round trip
+// 593 / 524).  An array of 8 columns is one tile.
+template <int N, bool NORM>
 int run_cols(const DeviceTables* t, const Addr& a, int64_t batch, int cols, int dir, hipStream_t s)
 {
-    if (cols < 16) return run_dir<N, true, 4>(t, a, batch, cols, cols, 1, dir, s);
-    if (dir == DCT2D_ROUNDTRIP) return run<N, DCT2D_ROUNDTRIP, true, 8>(t, a, batch, cols, cols, 1, s);
+    if (cols < 16) return run_dir<N, true, 4, NORM>(t, a, batch, cols, cols, 1, dir, s);
+    if (dir == DCT2D_ROUNDTRIP) return run<N, DCT2D_ROUNDTRIP, true, 8, NORM>(t, a, batch, cols, cols, 1, s);
     if constexpr (N <= 512) {
         if (cols >= 32)
-            return dir == DCT2D_FORWARD ? run<N, DCT2D_FORWARD, true, 16>(t, a, batch, cols, cols, 1, s)
-                                        : run<N, DCT2D_INVERSE, true, 16>(t, a, batch, cols, cols, 1, s);
+            return dir == DCT2D_FORWARD ? run<N, DCT2D_FORWARD, true, 16, NORM>(t, a, batch, cols, cols, 1, s)
+                                        : run<N, DCT2D_INVERSE, true, 16, NORM>(t, a, batch, cols, cols, 1, s);
     }
-    return dir == DCT2D_FORWARD ? run<N, DCT2D_FORWARD, true, 8>(t, a, batch, cols, cols, 1, s)
-                                : run<N, DCT2D_INVERSE, true, 8>(t, a, batch, cols, cols, 1, s);
+    return dir == DCT2D_FORWARD ? run<N, DCT2D_FORWARD, true, 8, NORM>(t, a, batch, cols, cols, 1, s)
+                                : run<N, DCT2D_INVERSE, true, 8, NORM>(t, a, batch, cols, cols, 1, s);
+}
+
+template <int N, bool NORM>
+int run_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass, int dir, hipStream_t s)
+{
+    return column_pass ? run_cols<N, NORM>(t, a, batch, cols, dir, s)
+                       : run_dir<N, false, 1, NORM>(t, a, batch, rows, 1, cols, dir, s);
 }
 
 } // namespace
@@ -265,7 +274,7 @@ int run_cols(const DeviceTables* t, const Addr& a, int64_t batch, int cols, int 
 bool line_axis(int n) { return is_pow2(n) || mix_smooth(n); }
 
 int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int rows, int cols, bool column_pass,
-                     int dir, hipStream_t s)
+                     int dir, bool norm, hipStream_t s)
 {
     const int len = column_pass ? rows : cols;
     // a pair of rows needs an even number of them; k_mix takes any
@@ -273,15 +282,15 @@ int launch_line_axis(const DeviceTables* t, const Addr& a, int64_t batch, int ro
         return launch_mix_axis(t, a, batch, rows, cols, column_pass, dir, s);
     switch (len) {
     case 1024:
-        return column_pass ? run_cols<1024>(t, a, batch, cols, dir, s)
-                           : run_dir<1024, false, 1>(t, a, batch, rows, 1, cols, dir, s);
+        return norm ? run_axis<1024, true>(t, a, batch, rows, cols, column_pass, dir, s)
+                    : run_axis<1024, false>(t, a, batch, rows, cols, column_pass, dir, s);
     case 512:
-        return column_pass ? run_cols<512>(t, a, batch, cols, dir, s)
-                           : run_dir<512, false, 1>(t, a, batch, rows, 1, cols, dir, s);
+        return norm ? run_axis<512, true>(t, a, batch, rows, cols, column_pass, dir, s)
+                    : run_axis<512, false>(t, a, batch, rows, cols, column_pass, dir, s);
     case 256:
-        return column_pass ? run_cols<256>(t, a, batch, cols, dir, s)
-                           : run_dir<256, false, 1>(t, a, batch, rows, 1, cols, dir, s);
-    default: return launch_short_line_pass(t, a, batch, len, column_pass ? cols : rows, column_pass, dir, s);
+        return norm ? run_axis<256, true>(t, a, batch, rows, cols, column_pass, dir, s)
+                    : run_axis<256, false>(t, a, batch, rows, cols, column_pass, dir, s);
+    default: return launch_short_line_pass(t, a, batch, len, column_pass ? cols : rows, column_pass, dir, norm, s);
     }
 }
 
@@ -291,8 +300,8 @@ int launch_long(const DeviceTables* t, const Job& j)
     const Addr first = j.addr();
     const Addr in_place{j.out, j.out, j.out_stride, j.out_stride, j.out_idx, j.out_idx, j.out_slot, j.out_slot};
     // rows first (input -> output), then columns in place on the output
-    int rc = launch_line_axis(t, first, j.batch, j.rows, j.cols, false, j.dir, j.stream);
-    if (rc == DCT2D_OK) rc = launch_line_axis(t, in_place, j.batch, j.rows, j.cols, true, j.dir, j.stream);
+    int rc = launch_line_axis(t, first, j.batch, j.rows, j.cols, false, j.dir, false, j.stream);
+    if (rc == DCT2D_OK) rc = launch_line_axis(t, in_place, j.batch, j.rows, j.cols, true, j.dir, false, j.stream);
     return rc;
 }
 

@@ -40,6 +40,7 @@ struct MixArgs {
     const float2* tab;
     const float2* prime;       // factors of the large prime radices
     int prime_at[kMixStages];  // where those of each stage's begin
+    float down, up;            // 2^-e, 2^e (see k_mix)
 };
 
 // LDS: the table (W, then c) from byte 0, then value e of slot l at (e * SLOTS + l).
@@ -208,13 +209,22 @@ __device__ __forceinline__ void mix_dft(uint32_t zb, const MixArgs& g)
 __device__ __forceinline__ int v_of(int j, int n) { return j & 1 ? n - 1 - (j >> 1) : j >> 1; }
 
 // The inverse transform is the forward DFT with real and imaginary parts exchanged at both ends.
+//
+// Range: no intermediate value is much larger than the result can be, as in a product with Q_n.  Forward, the
+// lines enter times 2^-e, 1 / sqrt n to 2 / sqrt n, which the factors c_k undo (unscaled, a constant image of 5e35 in
+// 512 x 384, whose largest coefficient is 2.2e38, came out as infinities).  Inverse, c_k, about 0.7 / sqrt n,
+// comes first and does this by itself.
 template <int DIR, bool COLS, int SLOTS, int NT>
 __global__ void __launch_bounds__(NT, 4) k_mix(MixArgs g)
 {
     const int n = g.plan.n, half = n / 2 + 1;
     const uint32_t cb = 8u * (uint32_t)n, zb = (cb + 8u * (uint32_t)half + 15u) & ~15u;
     const DCT_GLOBAL float2* tab = (const DCT_GLOBAL float2*)g.tab;
-    for (int i = threadIdx.x; i < n + half; i += NT) lds2(8u * (uint32_t)i) = tab[i];
+    for (int i = threadIdx.x; i < n + half; i += NT) {
+        float2 f = tab[i];
+        if (DIR == DCT2D_FORWARD && i >= n) f = make_float2(f.x * g.up, f.y * g.up);
+        lds2(8u * (uint32_t)i) = f;
+    }
 
     // column tiles: 16 neighbours share an XCD
     uint32_t blk = blockIdx.x;
@@ -262,7 +272,10 @@ __global__ void __launch_bounds__(NT, 4) k_mix(MixArgs g)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int j = threadIdx.x / SLOTS + NT / SLOTS * i;
-            if (j < n) val(DIR == DCT2D_INVERSE ? j : v_of(j, n), slot) = f[i];
+            if (j < n) {
+                if constexpr (DIR == DCT2D_INVERSE) val(j, slot) = f[i];
+                else val(v_of(j, n), slot) = make_float2(f[i].x * g.down, f[i].y * g.down);
+            }
         }
     } else {
         float4 fa[QI], fb[QI];
@@ -283,7 +296,11 @@ __global__ void __launch_bounds__(NT, 4) k_mix(MixArgs g)
         for (int i = 0; i < QI; ++i) {
             int l, q4;
             if (item(i, l, q4)) {
-                const float4 a = fa[i], b = fb[i];
+                float4 a = fa[i], b = fb[i];
+                if constexpr (DIR != DCT2D_INVERSE) {
+                    a = make_float4(a.x * g.down, a.y * g.down, a.z * g.down, a.w * g.down);
+                    b = make_float4(b.x * g.down, b.y * g.down, b.z * g.down, b.w * g.down);
+                }
                 const int e0 = DIR == DCT2D_INVERSE ? 4 * q4 : 2 * q4, e1 = DIR == DCT2D_INVERSE ? e0 + 1 : n - 1 - 2 * q4;
                 const int e2 = DIR == DCT2D_INVERSE ? e0 + 2 : e0 + 1, e3 = DIR == DCT2D_INVERSE ? e0 + 3 : e1 - 1;
                 val(e0, l) = make_float2(a.x, b.x);
@@ -303,7 +320,8 @@ __global__ void __launch_bounds__(NT, 4) k_mix(MixArgs g)
         const float2 zl = plo, zh = phi, ck = lds2(cb + 8u * (uint32_t)k);
         cf xa, xb, lo, hi;
         if constexpr (DIR != DCT2D_INVERSE) {
-            line::slot_forward<0>({zl.x, zl.y}, {zh.x, zh.y}, false, ck, 0.f, xa, xb);
+            const float2 cu = DIR == DCT2D_FORWARD ? ck : make_float2(ck.x * g.up, ck.y * g.up);
+            line::slot_forward<0>({zl.x, zl.y}, {zh.x, zh.y}, false, cu, 0.f, xa, xb);
         } else {
             xa = {zl.x, zh.x};
             xb = {zl.y, zh.y};
@@ -416,6 +434,9 @@ int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int row
     g.prime = t->prime_tab;
     for (int i = 0; i < g.plan.stages; ++i)
         if (g.plan.radix[i] > 16) g.prime_at[i] = prime_offset(g.plan.radix[i]);
+    g.up = 1.f;
+    while (4.f * g.up * g.up <= n) g.up *= 2.f; // the largest power of two up to sqrt n
+    g.down = 1.f / g.up;
     g.per_array = (uint32_t)((g.lines + 1) / 2);
     const int64_t total = batch * g.per_array;
     if (total > 0x7fffffff) return DCT2D_ERR_ARG;

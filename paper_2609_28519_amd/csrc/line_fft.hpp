@@ -55,6 +55,8 @@ struct LineCfg {
     static constexpr int TAB = N + N / 2, MID = TAB;             // entries kept in LDS
     static constexpr int SH = line_scale(N) == 0.25f ? 2 : line_scale(N) == 0.125f ? 3 : 4; // S = 2^-SH
     static_assert(line_scale(N) * (1 << SH) == 1.f, "S is a power of two");
+    // normalised transforms (NORM below): halvings at the end of the forward's first stage, 2^-SHN <= 1 / sqrt N
+    static constexpr int SHN = SH + 1;
 };
 
 namespace line {
@@ -270,15 +272,27 @@ struct Twiddles {
     __device__ __forceinline__ float2 slot(int q, int t) const { return tab[N + q * C::TPL + t]; }
 };
 
+// NORM: no intermediate value is much larger than the result can be, at the price of a few bits of
+// subnormal arrays.  Forward, the first stage (sums of 16 values) multiplies by 2^-SHN instead of the last
+// by S; inverse, the table's factors are reduced to c_k first.  fwd_c, inv_c: what the table's factors and
+// the unpaired coefficients' then take.
+template <int N, bool NORM>
+struct Norm {
+    using C = LineCfg<N>;
+    static constexpr int FIRST = NORM ? C::SHN : 0, LAST = NORM ? 0 : C::SH, INV_LAST = NORM ? 0 : C::SH;
+    static constexpr float fwd_c = NORM ? (float)(1 << (C::SHN - C::SH)) : 1.f;
+    static constexpr float inv_c = NORM ? 1.f / (1 << C::SH) : 1.f;
+};
+
 // Forward: v[i * R1 + m] = z[r1_of(i) + T1 m]  ->  v[16 i + q] = S Z[j3_of(i) + T3 q].
-template <int N, class P, class SYNC>
+template <int N, class P, bool NORM = false, class SYNC>
 __device__ __forceinline__ void fft_forward(cf (&v)[32], float* lds, int t, int ps, const Twiddles<N>& w, SYNC sync)
 {
     using C = LineCfg<N>;
     constexpr int R1 = C::R1, R2 = C::R2;
 #pragma unroll
     for (int i = 0; i < C::NB; ++i) {
-        dft<R1, false>(v + i * R1);
+        dft<R1, false, Norm<N, NORM>::FIRST>(v + i * R1);
         w.template stage1<false>(v + i * R1, r1_of<N>(t, i));
     }
     if constexpr (R2 > 1) {
@@ -305,12 +319,12 @@ __device__ __forceinline__ void fft_forward(cf (&v)[32], float* lds, int t, int 
             lds, v, [&](int i) { return P::ex2(i % R1, r1_of<N>(t, i / R1), ps); },
             [&](int i) { return P::ex2(j3_of<N>(t, i / 16), i % 16, ps); }, sync);
     }
-    dft16<false, C::SH>(v);
-    dft16<false, C::SH>(v + 16);
+    dft16<false, Norm<N, NORM>::LAST>(v);
+    dft16<false, Norm<N, NORM>::LAST>(v + 16);
 }
 
 // The transposed graph: v[16 i + q] = Z[j3_of(i) + T3 q]  ->  v[i * R1 + m] = S z[r1_of(i) + T1 m].
-template <int N, class P, class SYNC>
+template <int N, class P, bool NORM = false, class SYNC>
 __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int ps, const Twiddles<N>& w, SYNC sync)
 {
     using C = LineCfg<N>;
@@ -344,7 +358,7 @@ __device__ __forceinline__ void fft_inverse(cf (&v)[32], float* lds, int t, int 
 #pragma unroll
     for (int i = 0; i < C::NB; ++i) {
         w.template stage1<true>(v + i * R1, r1_of<N>(t, i));
-        dft<R1, true, C::SH>(v + i * R1);
+        dft<R1, true, Norm<N, NORM>::INV_LAST>(v + i * R1);
     }
 }
 
