@@ -1967,7 +1967,9 @@ int fp32_default_variant(int rows, int cols, int dir)
 int fp32_unshared_variant(int rows, int cols, int v)
 {
     if (rows <= 64 && cols <= 64) return v == 0 ? 3 : v;
-    if (tile_shape(rows, cols) && v > fp32_tile_variant(rows, cols)) return v - 1;
+    // k_tile and its looping form, or k_band, which come after the variants below whatever their number (128 x
+    // 256 and 256 x 128: 1023 arrays forward 150 and 168 us as k_rect256, 52 and 64 as k_tile)
+    if (v >= fp32_tile_variant(rows, cols)) return fp32_tile_variant(rows, cols);
     if (rows == 128 && cols == 128) return v == 0 ? 5 : v == 3 ? 4 : v;
     if (rows == 256 && cols == 256) return v == 0 || v == 3 || v == 4 ? 2 : v;
     if ((rows == 256) != (cols == 256)) return v == 2 || v == 3 ? 0 : v;
