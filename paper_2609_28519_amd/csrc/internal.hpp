@@ -213,6 +213,9 @@ int fp32_variant_count(int rows, int cols, int dir);
 int fp32_default_variant(int rows, int cols, int dir);
 int fp32_unshared_variant(int rows, int cols, int variant);
 
+// Ragged plans (ragged.cpp): whether the classes of a batch are recorded one after another, not as branches.
+bool records_as_chain(int64_t floats, int nodes);
+
 int launch_mfma(const DeviceTables* t, const Job& j, int precision);
 int mfma_supported(int rows, int cols, int precision);
 int mfma_variant_count(int rows, int cols, int dir, int precision);

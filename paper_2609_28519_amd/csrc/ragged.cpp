@@ -52,15 +52,22 @@ bool image_shape(int r, int c) { return !fast_shape(r, c) && !long_shape(r, c); 
 // a height that takes the dense product, which cannot run in place
 bool workspace_shape(int r, int c) { return image_shape(r, c) && !line_axis(r); }
 
-// Batches up to this many floats record their classes one after another.  The branches of a fork cross
-// queues, and a graph of them takes 83 - 105 us to run however little they do; a chain of 8 classes
-// takes 67 us (700 blocks, 1.8 million floats) and 76 (3000 blocks, 6.7 million), but 119 against 92
-// - 109 at 10,000 blocks (25 million), where the branches' work starts to overlap.
-constexpr int64_t kChainFloats = int64_t(1) << 23;
+// Kernel launches that a class records.
+int class_nodes(int rows, int cols, int dir)
+{
+    if (fast_shape(rows, cols)) return 1;
+    return workspace_shape(rows, cols) && dir == DCT2D_ROUNDTRIP ? 3 : 2;
+}
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 } // namespace
+
+// Whether a plan records its classes one after another.  The branches of a fork cross queues, and a graph of them
+// takes 60 us or more however little they do and 4 us more per node; a node of a chain takes 7 us and
+// keeps nothing else busy.  Forward, us, chain / fork: 8 nodes 58 / 105 (0.3 million floats), 60 / 71 (3
+// million), 71 / 79 (8 million), 82 / 80 (14 million); 12 nodes 108 / 84 (3 million); 36 nodes 282 / 144.
+bool dct::records_as_chain(int64_t floats, int nodes) { return floats <= (int64_t(1) << 23) && nodes <= 8; }
 
 struct dct2d_ragged_plan {
     int device = -1;
@@ -146,8 +153,10 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     std::sort(spans.begin(), spans.end());
     for (size_t i = 1; i < spans.size(); ++i)
         if (spans[i].first < spans[i - 1].second) return DCT2D_ERR_ARG; // overlapping arrays
+    int nodes = 0;
     for (auto& g : groups) {
         const bool fast = fast_shape(g.first.first, g.first.second);
+        nodes += class_nodes(g.first.first, g.first.second, dir);
         if (!fast && g.second.size() > 65535) return DCT2D_ERR_ARG;
         if (fast && precision != DCT2D_FP32 && precision != DCT2D_AUTO &&
             !mfma_supported(g.first.first, g.first.second, precision))
@@ -227,7 +236,7 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
         return DCT2D_ERR_HIP;
     }
     // record the graph: fork one branch per class from s0, join back; a small batch as a chain
-    const bool chain = floats <= kChainFloats;
+    const bool chain = records_as_chain(floats, nodes);
     const size_t ncls = p->cls.size();
     p->streams.resize(ncls + 1, nullptr);
     p->events.resize(ncls + 1, nullptr);

@@ -1,5 +1,5 @@
 """The rules that choose kernels on the host, called in the built library without a GPU: which variant a
-ragged plan runs where the policy names another."""
+ragged plan runs where the policy names another, and which plans record their classes as a chain."""
 import ctypes
 
 import pytest
@@ -37,3 +37,12 @@ def test_every_late_variant_maps_to_its_one_array_form(h, w):
     first = _rule("fp32_tile_variant", h, w)
     for v in range(first, _rule("fp32_variant_count", h, w, 0)):
         assert _rule("fp32_unshared_variant", h, w, v) == first, (h, w, v)
+
+
+def test_plans_of_many_classes_are_not_chained():
+    """A chain takes 7 us per kernel, so only few classes and little data make one."""
+    fn = dct.load()._ZN3dct16records_as_chainEli
+    fn.restype = ctypes.c_bool
+    chain = lambda floats, nodes: fn(ctypes.c_int64(floats), ctypes.c_int(nodes))  # noqa: E731
+    assert chain(1 << 20, 1) and chain(1 << 23, 8)
+    assert not chain((1 << 23) + 1, 8) and not chain(1 << 20, 9) and not chain(1 << 18, 36)
