@@ -104,9 +104,11 @@ _current = None
 
 def _find_current():
     """The call that returns the raw handle of the calling thread's current stream.  torch.cuda's
-    current_stream() builds a Stream object for it (2.9 us, a third of a small call)."""
+    current_stream() builds a Stream object for it (2.9 us, a third of a small call); it is asked once per
+    process, which makes its checks (a usable GPU, a process not forked from one that used it)."""
     global _current
     import torch
+    torch.cuda.current_stream()
     raw, dev = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
     if raw is None or dev is None:
         _current = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
@@ -115,10 +117,18 @@ def _find_current():
     return _current
 
 
+def _forget_current():
+    global _current
+    _current = None
+
+
+os.register_at_fork(after_in_child=_forget_current)
+
+
 def _stream(stream):
     if stream is None:
         return (_current or _find_current())()
-    return getattr(stream, "cuda_stream", stream)
+    return ctypes.c_void_p(getattr(stream, "cuda_stream", stream))  # whole numbers only
 
 
 def _geometry(t, rows, cols, stride, batch=None):
