@@ -46,6 +46,11 @@ std::map<std::pair<int, int>, float*> g_q;
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
+// Images per launch of the passes without a workspace.  A launch holds fewer than 2^32 threads and the line
+// kernels count their tiles in 31 bits; a pass has at most a thread per 7 values (33 x 33: 32 pairs to
+// 256 threads) and a pair to at least 14, so 2^34 values at a time stay inside both.
+int64_t line_chunk(int rows, int cols) { return (int64_t(1) << 34) / ((int64_t)rows * cols); }
+
 bool fast_shape(int r, int c) { return is_pow2(r) && is_pow2(c) && r >= 8 && r <= 256 && c >= 8 && c <= 256; }
 // power-of-two shapes with an axis of 512 or 1024: two line passes (no workspace)
 bool long_shape(int r, int c) { return is_pow2(r) && is_pow2(c) && r >= 8 && c >= 8 && r <= 1024 && c <= 1024 && (r > 256 || c > 256); }
@@ -145,6 +150,24 @@ int dct::launch_image(const DeviceTables* t, const Job& j, float* ws, const floa
     return rc == DCT2D_OK ? line(out, false) : rc;
 }
 
+namespace {
+
+// launch_image on `per` images at a time.
+int launch_chunks(const DeviceTables* t, const Job& job, int64_t per, float* ws, const float* q_rows)
+{
+    int rc = DCT2D_OK;
+    for (int64_t b0 = 0; b0 < job.batch && rc == DCT2D_OK; b0 += per) {
+        Job j = job;
+        j.batch = job.batch - b0 < per ? job.batch - b0 : per;
+        j.in = job.in + b0 * job.in_stride;
+        j.out = job.out + b0 * job.out_stride;
+        rc = launch_image(t, j, ws, q_rows);
+    }
+    return rc;
+}
+
+} // namespace
+
 int dct::image_scratch_init(int device)
 {
     if (device < 0 || device >= kMaxDevices) return DCT2D_ERR_NOINIT;
@@ -194,7 +217,7 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
         return launch_long(t, j);
     }
     Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
-    if (line_axis(rows)) return launch_image(t, j, nullptr, nullptr);
+    if (line_axis(rows)) return launch_chunks(t, j, line_chunk(rows, cols), nullptr, nullptr);
     const float* q_rows = cached_q(t->device, rows, &rc);
     if (!q_rows) return rc;
     const int64_t n = (int64_t)rows * cols;
@@ -202,12 +225,7 @@ int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, i
     float* ws = nullptr;
     if (hipMallocAsync(reinterpret_cast<void**>(&ws), (size_t)(per * n) * sizeof(float), s) != hipSuccess)
         return DCT2D_ERR_NOMEM;
-    for (int64_t b0 = 0; b0 < batch && rc == DCT2D_OK; b0 += per) {
-        j.batch = batch - b0 < per ? batch - b0 : per;
-        j.in = in + b0 * in_stride;
-        j.out = out + b0 * out_stride;
-        rc = launch_image(t, j, ws, q_rows);
-    }
+    rc = launch_chunks(t, j, per, ws, q_rows);
     if (hipFreeAsync(ws, s) != hipSuccess && rc == DCT2D_OK) rc = DCT2D_ERR_HIP;
     return rc;
 }
@@ -230,7 +248,7 @@ int dct2d_image_transform_noalloc(int dir, const float* in, float* out, int64_t 
         return launch_long(t, j);
     }
     Job j{dir, in, out, batch, rows, cols, in_stride, out_stride, s, 0};
-    if (line_axis(rows)) return launch_image(t, j, nullptr, nullptr);
+    if (line_axis(rows)) return launch_chunks(t, j, line_chunk(rows, cols), nullptr, nullptr);
     float* base = scratch_ptr(&rc);
     if (!base) return rc;
     const size_t n = (size_t)rows * cols;
@@ -244,13 +262,7 @@ int dct2d_image_transform_noalloc(int dir, const float* in, float* out, int64_t 
     // the table is rebuilt on the caller's stream every call: the scratch keeps whatever the previous
     // call on this device left in it
     rc = tables_dense_q(rows, q_rows, s);
-    for (int64_t b0 = 0; b0 < batch && rc == DCT2D_OK; b0 += per) {
-        j.batch = batch - b0 < per ? batch - b0 : per;
-        j.in = in + b0 * in_stride;
-        j.out = out + b0 * out_stride;
-        rc = launch_image(t, j, ws, q_rows);
-    }
-    return rc;
+    return rc == DCT2D_OK ? launch_chunks(t, j, per, ws, q_rows) : rc;
 }
 
 } // extern "C"
