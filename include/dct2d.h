@@ -259,7 +259,8 @@ int dct2d_ragged_plan_info(const dct2d_ragged_plan* plan, int64_t* items, int32_
  * the path's error band (single-pass and BF16X3).  A candidate that fails is never
  * frozen; if every candidate fails, dct2d_tune returns DCT2D_ERR_HIP and leaves the
  * table unchanged.  dct2d_get_variant / dct2d_set_variant read and override the
- * frozen table; dct2d_variant_count gives the number of candidates (0 = none).
+ * frozen table (where an entry was neither tuned nor set, a few shapes run another variant
+ * for batches too small to fill the device; dct2d_get_variant names that of large ones); dct2d_variant_count gives the number of candidates (0 = none).
  * `dir` may also be DCT2D_FILTER, with precision DCT2D_FP32 (or DCT2D_AUTO, which for the
  * filter always means DCT2D_FP32): the filter's own frozen variant, which starts as the
  * round trip's and is tuned on scratch data with one shared multiplier array. */

@@ -23,8 +23,10 @@ constexpr int kNumPrec = 8;
 
 // Frozen variant table: index [log2 rows - 3][log2 cols - 3][dir][precision] (dir 3: the
 // spectral filter, float32 only); starts from the per-size defaults (the variants measured
-// fastest on MI355X; the filter starts from the round trip's), overridable by the tuner.
-constexpr int kNumDir = 4;
+// fastest on MI355X; the filter starts from the round trip's), overridable by the tuner.  An entry
+// kDefault stands for the default, which for some shapes depends on the batch (fp32_default_variant).
+constexpr int kNumDir = 4, kDefault = -1;
+constexpr int64_t kLargeBatch = int64_t(1) << 62; // the batch whose default dct2d_get_variant names
 std::mutex g_policy_mu;
 int g_variant[6][6][kNumDir][kNumPrec];
 bool g_policy_ready = false;
@@ -36,8 +38,7 @@ void policy_init_locked()
         for (int c = 0; c < 6; ++c)
             for (int d = 0; d < kNumDir; ++d)
                 for (int p = 0; p < kNumPrec; ++p)
-                    g_variant[r][c][d][p] =
-                        p == DCT2D_FP32 ? fp32_default_variant(8 << r, 8 << c, d == DIR_FILTER ? DCT2D_ROUNDTRIP : d) : 0;
+                    g_variant[r][c][d][p] = p == DCT2D_FP32 ? kDefault : 0;
     g_policy_ready = true;
 }
 
@@ -62,11 +63,15 @@ bool long_axis_size_ok(int rows, int cols)
            (rows > 256 || cols > 256);
 }
 
-int variant_for(int rows, int cols, int dir, int prec)
+int variant_for(int rows, int cols, int dir, int prec, int64_t batch)
 {
-    std::lock_guard<std::mutex> lk(g_policy_mu);
-    policy_init_locked();
-    return g_variant[lg2(rows) - 3][lg2(cols) - 3][dir][prec];
+    int v;
+    {
+        std::lock_guard<std::mutex> lk(g_policy_mu);
+        policy_init_locked();
+        v = g_variant[lg2(rows) - 3][lg2(cols) - 3][dir][prec];
+    }
+    return v == kDefault ? fp32_default_variant(rows, cols, dir, batch) : v;
 }
 
 // DCT2D_AUTO: the float32-accurate path chosen per size.  Frozen before measurement
@@ -180,7 +185,7 @@ __global__ void k_fill(float* p, int64_t n, uint32_t seed)
 int dct::dispatch(const DeviceTables* t, Job j, int prec)
 {
     const int p = resolve_precision(j.rows, j.cols, j.dir, prec);
-    j.variant = variant_for(j.rows, j.cols, j.dir, p);
+    j.variant = variant_for(j.rows, j.cols, j.dir, p, j.batch);
     if (p == DCT2D_FP32) {
         if (j.shared) j.variant = fp32_unshared_variant(j.rows, j.cols, j.variant);
         return launch_fp32(t, j);
@@ -254,7 +259,7 @@ int dct2d_filter(const float* in, float* out, int64_t batch, int32_t rows, int32
     // a fused round-trip kernel with the multiply between the passes, in the filter's own
     // frozen variant
     Job j{DIR_FILTER, in, out, batch, rows, cols, in_stride, out_stride, static_cast<hipStream_t>(stream),
-          variant_for(rows, cols, DIR_FILTER, DCT2D_FP32)};
+          variant_for(rows, cols, DIR_FILTER, DCT2D_FP32, batch)};
     j.lam = lambda;
     j.lam_stride = lambda_stride;
     return launch_fp32(t, j);
@@ -274,7 +279,7 @@ int dct2d_get_variant(int32_t rows, int32_t cols, int dir, int precision)
     if (dir == DCT2D_FILTER && precision != DCT2D_FP32 && precision != DCT2D_AUTO) return DCT2D_ERR_PRECISION;
     // for DCT2D_AUTO the "variant" is the frozen path (a dct2d_precision value)
     if (precision == DCT2D_AUTO) return dir == DCT2D_FILTER ? DCT2D_FP32 : resolve_precision(rows, cols, dir, DCT2D_AUTO);
-    return variant_for(rows, cols, dir, precision);
+    return variant_for(rows, cols, dir, precision, kLargeBatch);
 }
 
 int dct2d_set_variant(int32_t rows, int32_t cols, int dir, int precision, int variant)
@@ -405,7 +410,7 @@ int dct2d_tune(int32_t rows, int32_t cols, int dir, int precision, int64_t batch
             if (dir == DCT2D_FORWARD || dir == DCT2D_INVERSE) {
                 Job back{dir == DCT2D_FORWARD ? DCT2D_INVERSE : DCT2D_FORWARD, dst, chk, batch, rows, cols, per, per,
                          s, variant_for(rows, cols, dir == DCT2D_FORWARD ? DCT2D_INVERSE : DCT2D_FORWARD,
-                                        DCT2D_FP32)};
+                                        DCT2D_FP32, batch)};
                 if ((rc = launch_fp32(t, back)) != DCT2D_OK) break;
                 res = chk;
             }

@@ -210,7 +210,7 @@ int launch_tile(const DeviceTables* t, const Job& j, bool persistent);
 bool band_shape(int rows, int cols);
 int launch_band(const DeviceTables* t, const Job& j);
 int fp32_variant_count(int rows, int cols, int dir);
-int fp32_default_variant(int rows, int cols, int dir);
+int fp32_default_variant(int rows, int cols, int dir, int64_t batch); // dir: DIR_FILTER too
 int fp32_unshared_variant(int rows, int cols, int variant);
 
 // Ragged plans (ragged.cpp): whether the classes of a batch are recorded one after another, not as branches.

@@ -1918,14 +1918,52 @@ int fp32_variant_count(int rows, int cols, int)
     return fp32_tile_variant(rows, cols) + (tile_shape(rows, cols) ? 2 : band_shape(rows, cols) ? 1 : 0);
 }
 
+// Batches that another variant than that of large ones leads on.  Kernels that give a wavefront more arrays, or
+// an array more steps that wait on one another, are ahead only where the chip is full; and k_fused (four
+// arrays of 4096 to 8192 values per CU) and k_rect256 (two of 16384) run up to 1024 and 512 arrays at
+// once, which the last part of that range is better off with.  us, the large batches' default against this one:
+//   k_pack / wave-local kernel (the same arithmetic, bit for bit): 8 x 64 forward 7.7 / 5.7 (128 arrays), 9.1 / 7.8
+//     (4096), 10.8 / 12.4 (8192), round trip 10.1 / 8.3 (2048), 11.2 / 11.5 (4096); 16 x 64 round trip 9.2 / 6.5
+//     (64 arrays), 10.6 / 8.5 (2048), 13.1 / 13.3 (4096)
+//   wave-local kernel with a cap on resident workgroups / without (bit for bit): 32 x 64 forward 15.0 / 11.5
+//     (3072 arrays), 18.2 / 15.4 (4096), 26.9 / 26.8 (8192)
+//   k_band / k_fused: 8 x 128 forward 8.4 / 7.1 (256 arrays), 8.5 / 8.8 (512); 128 x 8 filter 14.0 / 10.9, 14.1 / 14.9;
+//     128 x 16 filter 13.7 / 16.0 (512), 15.0 / 13.3 (1024)
+//   k_tile / k_fused: 128 x 64 round trip 20.8 / 19.0 (430 arrays), 32.7 / 27.3 (1024), 34.7 / 42.8 (1217); 32 x 128
+//     filter 20.8 / 17.2 (1024), 21.2 / 30.5 (1217); 128 x 32 inverse 14.8 / 11.9, 16.2 / 21.2
+//   k_tile / k_rect256: 256 x 64 round trip 33.9 / 29.9 (512 arrays), 39.5 / 48.0 (608), filter 22.3 / 20.5 (32), 36.4 / 30.6
+//     (512), 47.3 / 49.3 (608)
+struct FewArrays {
+    int rows, cols, dirs; // bit d: direction d
+    int64_t first, last;  // batches
+    int variant;
+};
+constexpr int kBoth = 1 << DCT2D_ROUNDTRIP | 1 << DIR_FILTER, kOneWay = 1 << DCT2D_FORWARD | 1 << DCT2D_INVERSE;
+constexpr FewArrays kFewArrays[] = {
+    {8, 64, kOneWay, 1, 6143, 4}, {64, 8, kOneWay, 1, 6143, 4},
+    {8, 64, kBoth, 1, 4095, 4}, {64, 8, kBoth, 1, 4095, 4},
+    {16, 64, kBoth, 1, 4095, 4}, {64, 16, kBoth, 1, 4095, 4},
+    {32, 64, kOneWay, 1, 4096, 4}, {64, 32, kOneWay, 1, 4096, 4},
+    {8, 128, kOneWay, 1, 511, 0}, {128, 8, kOneWay | kBoth, 1, 511, 0},
+    {128, 16, 1 << DCT2D_INVERSE | kBoth, 800, 1024, 0},
+    {128, 64, 1 << DCT2D_INVERSE | 1 << DCT2D_ROUNDTRIP, 400, 1024, 0},
+    {128, 32, 1 << DCT2D_INVERSE | 1 << DCT2D_ROUNDTRIP, 512, 1024, 0},
+    {32, 128, 1 << DCT2D_INVERSE | kBoth, 800, 1024, 0},
+    {64, 128, 1 << DIR_FILTER, 700, 1024, 0},
+    {256, 64, kBoth, 1, 512, 0}, {256, 32, 1 << DIR_FILTER, 800, 1024, 0},
+};
+
 // Variant used until the tuner measures otherwise (fastest in measurements on MI355X
 // with 512 MiB batches), by the longer axis of arrays up to 64 x 64: 8 staged; 16 staged
 // with at most 16 workgroups per CU; 32 at most 10 per CU, staged for the round trip;
 // 64 x 64 the two-wavefront split kernel, with at most 4 workgroups per CU for forward and
 // inverse.  The staged split kernel for 128 x 128 with one array per workgroup; the
 // whole-array register kernel for the other shapes with an axis of 128 or 256 and none below 32.
-int fp32_default_variant(int rows, int cols, int dir)
+int fp32_default_variant(int rows, int cols, int dir, int64_t batch)
 {
+    for (const FewArrays& f : kFewArrays)
+        if (f.rows == rows && f.cols == cols && (f.dirs >> dir & 1) && batch >= f.first && batch <= f.last) return f.variant;
+    if (dir == DIR_FILTER) dir = DCT2D_ROUNDTRIP;
     if (rows <= 64 && cols <= 64) {
         const int m = rows > cols ? rows : cols;
         const bool rt = dir == DCT2D_ROUNDTRIP;

@@ -21,6 +21,9 @@ def _run(x, direction):
     import torch
     import paper_2609_28519_amd as dct
     dct.init(0)
+    h, w = x.shape[1:]
+    if max(h, w) <= 256:  # the variant of large batches, whatever this one's size
+        dct.set_variant(h, w, direction, "fp32", dct.get_variant(h, w, direction, "fp32"))
     y = dct.transform(torch.from_numpy(x).cuda(), None, direction, "fp32")
     return y.cpu().numpy()
 
