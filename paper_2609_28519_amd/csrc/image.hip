@@ -6,7 +6,7 @@
 // (kern_line.hip).  Every other shape is computed exactly, without zero-padding, axis by axis
 // (launch_image): a power-of-two axis by the line kernels, other lengths (384, 600, 1000) by the
 // mixed-radix kernels (kern_mix.hip), each in place on the output; heights
-// p, 2p and 3p with a large prime p from the dense Q_n of eq. 1 (FP64-generated, rounded to float32,
+// p, 2p and 3p with a large prime p (mix_plan) from the dense Q_n of eq. 1 (FP64-generated, rounded to float32,
 // kern_dense.hip).  The dense pass writes its output tile from whole input columns, so it goes
 // through a workspace of one float32 image per image of the batch.
 //

@@ -1,8 +1,8 @@
 // Dense column pass for whole images: the transform of length L = rows along the columns of a batch
 // of h x w images, by a float32 matrix product with the dense Q_L of eq. 1 (Section 2.1; arbitrary
-// axes, Section 7.1).  Used for the few image heights that the line transforms leave out, p, 2p and
-// 3p with a large prime p (997, 998, 1011); zero-padding would change the transform.  (Widths are
-// multiples of 4 and never among them.)
+// axes, Section 7.1).  Used for the image heights that the line transforms leave out, p and 2p with a
+// prime p of 131 or more and 3p with one of 89 or more (252 of the lengths 8 .. 1024); zero-padding would
+// change the transform.  (Widths are multiples of 4 and never among them.)
 //
 // Q_L's even rows are symmetric and its odd rows antisymmetric about the middle, so with
 // E = ceil(L / 2)

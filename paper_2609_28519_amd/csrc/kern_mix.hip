@@ -19,8 +19,6 @@
 // 961 x 1020 (31, 17) 821 -> 87.
 #include <hip/hip_runtime.h>
 
-#include <array>
-
 #include "internal.hpp"
 #include "mix_fft.hpp"
 
@@ -393,8 +391,9 @@ int mix_run(const MixArgs& g, int dir, hipStream_t s)
 template <bool COLS>
 int mix_slots(const MixArgs& g, int dir, hipStream_t s)
 {
-    switch (mix_shape(g.plan.n).slots) {
-    case 8: return g.plan.n > 512 ? mix_run<COLS, 8, 512>(g, dir, s) : mix_run<COLS, 8, 256>(g, dir, s);
+    const MixShape shape = mix_shape(g.plan.n);
+    switch (shape.slots) {
+    case 8: return shape.threads == 512 ? mix_run<COLS, 8, 512>(g, dir, s) : mix_run<COLS, 8, 256>(g, dir, s);
     case 16: return mix_run<COLS, 16, 256>(g, dir, s);
     case 32: return mix_run<COLS, 32, 256>(g, dir, s);
     case 128: return mix_run<COLS, 128, 256>(g, dir, s);
@@ -403,16 +402,6 @@ int mix_slots(const MixArgs& g, int dir, hipStream_t s)
 }
 
 } // namespace
-
-static int prime_offset(int p)
-{
-    static const auto at = [] {
-        std::array<int, kMaxPrime + 1> o{};
-        for (int q = kMixRadix + 1; q < kMaxPrime; ++q) o[q + 1] = o[q] + (is_prime(q) ? prime_table_size(q) : 0);
-        return o;
-    }();
-    return at[p];
-}
 
 bool mix_smooth(int n)
 {
@@ -433,7 +422,7 @@ int launch_mix_axis(const DeviceTables* t, const Addr& a, int64_t batch, int row
     g.tab = t->mix_tab + mix_table_offset(n);
     g.prime = t->prime_tab;
     for (int i = 0; i < g.plan.stages; ++i)
-        if (g.plan.radix[i] > 16) g.prime_at[i] = prime_offset(g.plan.radix[i]);
+        if (g.plan.radix[i] > 16) g.prime_at[i] = prime_table_offset(g.plan.radix[i]);
     g.up = 1.f;
     while (4.f * g.up * g.up <= n) g.up *= 2.f; // the largest power of two up to sqrt n
     g.down = 1.f / g.up;

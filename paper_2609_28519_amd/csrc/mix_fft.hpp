@@ -40,13 +40,16 @@ constexpr bool is_prime(int p)
     return p > 1;
 }
 constexpr int prime_table_size(int p) { return (p / 2 + kPrimeBlock) / kPrimeBlock * (p / 2) * kPrimeBlock; }
-constexpr int prime_table_offset(int p)
-{
-    int o = 0;
-    for (int q = kMixRadix + 1; q < p; ++q)
-        if (is_prime(q)) o += prime_table_size(q);
-    return o;
-}
+// Where the table of each prime begins; the last entry is the size of all.
+struct PrimeOffsets {
+    int at[kMaxPrime + 2] = {};
+    constexpr PrimeOffsets()
+    {
+        for (int q = kMixRadix + 1; q <= kMaxPrime; ++q) at[q + 1] = at[q] + (is_prime(q) ? prime_table_size(q) : 0);
+    }
+};
+inline constexpr PrimeOffsets kPrimeOffsets;
+constexpr int prime_table_offset(int p) { return kPrimeOffsets.at[p]; }
 
 struct MixPlan {
     int n = 0, stages = 0;
@@ -57,8 +60,8 @@ struct MixPlan {
 
 // The radices of n: odd ones first (their strided writes touch all LDS banks), the largest power of
 // two last (its writes are contiguous).  False for lengths left to the dense products: those with a
-// prime factor so large that fewer than 32 butterflies (of the workgroup's pairs) share it, that is
-// p, 2p and 3p on the longest axes, where most lanes of the prime's pass would idle.
+// prime factor so large that fewer than 32 butterflies (of the workgroup's pairs) share it, where most
+// lanes of the prime's pass would idle: p and 2p from p = 131, 3p from p = 89, 252 lengths in all.
 inline bool mix_plan(int n, MixPlan& p)
 {
     p = MixPlan{};

@@ -6,11 +6,12 @@
 // configuration of the frozen per-size policy (the same table the autotuner fills for
 // the basic calls, Section 3.2: variants fixed before measurement), with grid-stride
 // schedules replaced by one tile per workgroup, since the classes share the GPU.  Image classes
-// run pass by pass in place on the batch, without a workspace; the few lengths that take dense
-// products (line_axis) get float32 Q tables, and their class a workspace.  The whole batch is then
+// run pass by pass in place on the batch, without a workspace; the heights that take dense
+// products (not line_axis) get float32 Q tables, and their class a workspace.  The whole batch is then
 // recorded once into a HIP graph: one fork-join branch per class, so independent
-// classes run concurrently (a small batch: one class after another).  Kernels read the batch base pointer from a plan-owned
-// device slot, so the recorded graph replays on any buffer.
+// classes run concurrently (a few classes of a small batch: one after another, records_as_chain).
+// Kernels read the batch base pointer from a plan-owned device slot, so the recorded graph replays
+// on any buffer.
 //
 // Execute: if the base differs from the one in the slot, one 8-byte copy updates the
 // slot (stream-ordered before the graph); then a single hipGraphLaunch.
@@ -112,7 +113,7 @@ int record_class(const DeviceTables* t, dct2d_ragged_plan* p, const ClassRec& c,
         Job j{p->dir, nullptr, nullptr, c.count, c.rows, c.cols, 0, 0, s, 0};
         j.in_idx = j.out_idx = c.d_off;
         j.in_slot = j.out_slot = p->d_slot;
-        j.shared = true; // the classes run as concurrent branches of the graph
+        j.shared = true; // beside the other classes (or one after another, where the two forms are alike)
         // long axes: float32 whatever the plan's precision (the split paths cover axes <= 256)
         if (c.long_axes) return launch_long(t, j);
         return dispatch(t, j, p->prec);
@@ -237,10 +238,10 @@ int dct2d_ragged_plan_create(const dct2d_block* blocks, int64_t count, int dir, 
     }
     // record the graph: fork one branch per class from s0, join back; a small batch as a chain
     const bool chain = records_as_chain(floats, nodes);
-    const size_t ncls = p->cls.size();
-    p->streams.resize(ncls + 1, nullptr);
-    p->events.resize(ncls + 1, nullptr);
-    for (size_t i = 0; i <= ncls; ++i) {
+    const size_t ncls = p->cls.size(), branches = chain ? 0 : ncls;
+    p->streams.resize(branches + 1, nullptr);
+    p->events.resize(branches + 1, nullptr);
+    for (size_t i = 0; i <= branches; ++i) {
         if (hipStreamCreateWithFlags(&p->streams[i], hipStreamNonBlocking) != hipSuccess ||
             hipEventCreateWithFlags(&p->events[i], hipEventDisableTiming) != hipSuccess) {
             release(p);

@@ -70,7 +70,14 @@ def test_few_arrays_run_the_variant_that_leads_there(h, w, direction, batch, few
     assert dct.get_variant(h, w, direction, "fp32") == many
 
 
-@pytest.mark.parametrize("h,w,direction,lo", [(128, 64, 1, 400), (128, 64, 2, 400), (128, 32, 1, 512), (32, 128, 3, 800),
-                                                    (128, 16, 3, 800), (64, 128, 3, 700)])
-def test_arrays_that_fill_the_chip_once(h, w, direction, lo):
-    assert [_default(h, w, direction, b) for b in (1, lo - 1, lo, 1024, 1025, LARGE)] == [2, 2, 0, 0, 2, 2]
+@pytest.mark.parametrize("h,w,direction,lo,hi", [(128, 64, 1, 400, 1024), (128, 64, 2, 560, 960), (128, 32, 1, 512, 1024),
+                                                 (32, 128, 3, 800, 1024), (128, 16, 3, 800, 1024), (64, 128, 3, 700, 900)])
+def test_arrays_that_fill_the_chip_once(h, w, direction, lo, hi):
+    assert [_default(h, w, direction, b) for b in (1, lo - 1, lo, hi, hi + 1, LARGE)] == [2, 2, 0, 0, 2, 2]
+
+
+@pytest.mark.parametrize("h,w", SHAPES)
+def test_round_trip_and_filter_run_the_same_variant(h, w):
+    """Multipliers of one give the round trip bit for bit, at every batch."""
+    for b in list(range(1, 1300)) + [4095, 4096, 6143, 6144, LARGE]:
+        assert _default(h, w, 2, b) == _default(h, w, 3, b), b
