@@ -172,12 +172,13 @@ int dct2d_filter(const float* in, float* out, int64_t batch, int32_t rows, int32
  * is computed exactly (the paper's own library rejects non-power-of-two axes, Section 7.1,
  * rather than zero-padding them, which would change the transform), one pass per axis, in place
  * on the output and without a workspace: mixed-radix transforms of the axis's own length.  The
- * exception are the 252 heights p and 2p with a prime p of 131 or more and 3p with one of 89 or
- * more (131, 262, 267, 997, ...): one dense float32 product with the Q_n of eq. 1 along the columns (two for the round trip), with the even/odd
- * level of Q_n's symmetry taken out.  It goes through a workspace of rows*cols floats per image
- * (batch images, at most 65535 at a time), taken from the stream-ordered allocator on `stream`
- * and released on it; the dense Q_n of each such height is built once per device on first use
- * (so the first call of it synchronises the device) and kept until dct2d_finalize.
+ * exception are the 252 heights p and 2p with a prime p of 131 or more and 3p with one of
+ * 89 or more (131, 262, 267, 997, ...): one dense float32 product with the Q_n of eq. 1
+ * along the columns (two for the round trip), with the even/odd level of Q_n's symmetry
+ * taken out.  It goes through a workspace of rows*cols floats per image (batch images, at
+ * most 65535 at a time), taken from the stream-ordered allocator on `stream` and released
+ * on it; the dense Q_n of each such height is built once per device on first use (so the
+ * first call of it synchronises the device) and kept until dct2d_finalize.
  * Errors: DCT2D_ERR_SIZE (shape), DCT2D_ERR_NOMEM (workspace), as dct2d_transform_ex
  * otherwise. */
 int dct2d_image_transform(int dir, const float* in, float* out, int64_t batch, int32_t rows,

@@ -9,10 +9,10 @@
 // Bound: HBM; the LDS tile allows two workgroups (8 wavefronts) per CU.
 // 2^27 floats, out of place, us, the best other variant -> this one, forward / inverse / round trip (the copy
 // ceiling is 176):
-//     8 x 128   468 451 698 -> 233 259 252     128 x 8    429 441 636 -> 241 231 311
-//    16 x 128   441 450 700 -> 210 223 252    128 x 16    432 435 654 -> 211 253 300
-//     8 x 256   284 263 438 -> 225 240 247     256 x 8    317 318 526 -> 232 229 326
-//    16 x 256   276 263 444 -> 200 209 261    256 x 16    322 301 537 -> 212 263 308
+//     8 x 128   468 451 698 -> 230 261 247     128 x 8    429 441 636 -> 242 240 321
+//    16 x 128   441 450 700 -> 216 222 251    128 x 16    432 435 654 -> 209 258 311
+//     8 x 256   284 260 443 -> 223 238 237     256 x 8    315 319 505 -> 229 234 317
+//    16 x 256   282 263 456 -> 202 205 239    256 x 16    328 301 511 -> 202 260 304
 #include "fp32_common.hpp"
 #include "line_fft.hpp"
 

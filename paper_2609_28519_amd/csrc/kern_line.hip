@@ -18,8 +18,9 @@
 //     neighbouring tiles run on the same XCD, whose L2 then sees whole 128-byte lines (1024 x 1024
 //     forward with 16-column tiles: 544 us apart, 432 us together).
 // 2^27 floats, out of place, us before -> now (forward / inverse / round trip):
-//   1024 x 1024  985 -> 435, 951 -> 430, 1622 -> 524      8 x 1024   819 -> 397, 786 -> 398, 1130 -> 442
-//   512 x 512    684 -> 422, 746 -> 426, 820 -> 480       1024 x 8   685 -> 400, 668 -> 408, 895 -> 462
+//   1024 x 1024  981 -> 439, 952 -> 431, 1626 -> 473      8 x 1024   815 -> 411, 773 -> 420, 1131 -> 424
+//   512 x 512    678 -> 421, 745 -> 424, 809 -> 449       1024 x 8   679 -> 399, 647 -> 395, 894 -> 412
+// Whole images run the normalised forms (Norm, line_fft.hpp), at the same speed.
 #include <hip/hip_runtime.h>
 
 #include "internal.hpp"

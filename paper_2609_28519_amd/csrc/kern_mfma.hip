@@ -718,9 +718,9 @@ __device__ __forceinline__ void tile_products(f32x16& acc, const V (&av)[3][2], 
 
 // Blocks enter and leave through a wavefront's staging area by whole 1 KB moves.  Read and written in
 // the operand layout itself (16 bytes of 32 rows per instruction) the kernel was bound by those
-// accesses whatever its arithmetic: us per 2^27 floats, forward / inverse, before -> now: bf16
-// 289/289 -> 210/208, fp16x3 265/256 -> 223/219, bf16x3 253/239 -> 221/216, fp8 249/247 -> 214/211, bf16x6
-// 300/267 -> 287/249 (192 matrix instructions and 1000 conversions per block bound that one).
+// accesses whatever its arithmetic: us per 2^27 floats, forward / inverse, out of place, before -> now: bf16
+// 283/283 -> 208/207, fp16x3 261/260 -> 216/217, bf16x3 230/235 -> 213/213, fp8 243/244 -> 209/209, bf16x6
+// 257/253 -> 236/229.
 // The staging area: half a block, 32 rows of 64, the 16-byte groups of row r XOR-permuted
 // by r mod 8 (both the row-wise and the lane-per-row accesses then touch every bank).
 __device__ __forceinline__ int stage64(int r, int group) { return r * 64 + 4 * (group ^ (r & 7)); }

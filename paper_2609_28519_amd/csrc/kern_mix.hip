@@ -12,8 +12,8 @@
 // million wave instructions on the vector ALU (about 100 us) and 10 to 14 million on LDS (60 to 110 us)
 // do not fully overlap with HBM at the 16 wavefronts per CU that the registers allow.
 // 2^25 floats, out of place, us, the dense products before -> now (forward / round trip):
-//   512 x 384  400 -> 140, 727 -> 190     600 x 1000  705 -> 186, 1287 -> 291
-//   768 x 768  619 -> 161, 1124 -> 247    720 x 480   570 -> 179, 1038 -> 269
+//   512 x 384  340 -> 123, 645 -> 146     600 x 1000  616 -> 153, 1193 -> 239
+//   768 x 768  532 -> 132, 1018 -> 196    720 x 480   480 -> 142, 923 -> 217
 // With a large prime factor the prime's pass is bound by the vector ALU, about R multiply-adds per
 // complex value; 10^7 floats, forward: 822 x 712 (137, 89) 583 -> 168 us, 1004 x 1004 (251) 807 -> 349,
 // 961 x 1020 (31, 17) 821 -> 87.

@@ -7,22 +7,23 @@
 //
 // Bound: HBM where several workgroups share a CU (64 x 256 and below: 5.3 TB/s forward), else the sum of
 // the phases.  A 256 x 256 array takes the whole register file of a CU, so loads, arithmetic and stores
-// of an array overlap only across its own 16 wavefronts: the round trip issues 139 million wave
-// instructions (180 us) and 125 us of LDS beside 177 us of HBM, and takes 393.
+// of an array overlap only across its own 16 wavefronts: the round trip issues 140 million wave
+// instructions (180 us) and 125 us of LDS beside 177 us of HBM, and takes 391.
 //   * 64 values per thread and at most 128 registers: 16 wavefronts per CU, twice those of k_split256
 //     and four times those of k_rect256_db.  Nothing may spill for that: at 300 bytes of scratch per
 //     thread the 256 x 256 round trip took 700 us, at 84 (the row pass's offsets held across the columns)
 //     403, and that of 128 x 256 346 instead of 295.
 //   * the LDS tile holds half an array: a transposition is two rounds (transpose below).
 // 2^27 floats, out of place, us, the best kernel before -> now (forward / inverse / round trip):
-//   256 x 256  292 -> 265, 303 -> 288, 432 -> 393    128 x 256  497 -> 210, 413 -> 208, 529 -> 295
-//   256 x 128  487 -> 230, 472 -> 222, 614 -> 315    64 x 256   284 -> 203, 279 -> 201, 462 -> 308
-//   256 x 64   284 -> 251, 260 -> 262, 473 -> 370    32 x 256   281 -> 195, 271 -> 197, 457 -> 257
-//   256 x 32   288 -> 218, 251 -> 252, 453 -> 326    64 x 128   424 -> 203, 425 -> 202, 478 -> 271
-//   128 x 64   426 -> 220, 424 -> 258, 490 -> 323    32 x 128   454 -> 208, 447 -> 202, 561 -> 275
-//   128 x 32   434 -> 208, 426 -> 261, 591 -> 294
-// (Tall arrays trail wide ones: eight threads share a column pair of 256 rows, so a wavefront covers 16
-// columns, 64 bytes of a row.)
+//   256 x 256  300 -> 255, 304 -> 284, 430 -> 391    128 x 256  496 -> 205, 424 -> 206, 535 -> 285
+//   256 x 128  487 -> 220, 476 -> 221, 620 -> 324    64 x 256   297 -> 203, 284 -> 205, 474 -> 259
+//   256 x 64   281 -> 257, 260 -> 262, 468 -> 334    32 x 256   288 -> 193, 268 -> 195, 476 -> 226
+//   256 x 32   291 -> 210, 251 -> 252, 450 -> 303    64 x 128   434 -> 202, 432 -> 199, 501 -> 250
+//   128 x 64   433 -> 217, 429 -> 255, 496 -> 316    32 x 128   454 -> 206, 486 -> 199, 579 -> 270
+//   128 x 32   482 -> 205, 479 -> 265, 587 -> 307
+// (Tall arrays trail wide ones.  Their rows are short: with W = 64 two lanes share a row pair, and a wavefront
+// instruction takes 16 bytes of each of 32 pairs; the 256 x 64 forward reads 1.3 to 1.5 times its input and writes
+// its output once.)
 #include <hip/hip_runtime.h>
 
 #include "internal.hpp"
